@@ -132,10 +132,10 @@ PrefillWs prefill_layout(const ssm_shard_desc_t* d, int64_t T, int nseq, void* b
     L.scan = take(scan_scratch_bytes(T, (int)E, nseq));
     const int adt = d->act_dtype;
     const int64_t dm = d->d_model, R = d->dt_rank;
-    size_t sk = gemm_splitk_bytes(T, 2 * E, dm, adt, adt, kGemmInProj);
-    sk = std::max(sk, gemm_splitk_bytes(T, W, E, adt, adt, kGemmXProj));
-    sk = std::max(sk, gemm_splitk_bytes(T, E, R, adt, adt, kGemmDtProj));
-    sk = std::max(sk, gemm_splitk_bytes(T, dm, E, adt, adt, kGemmOutProj));
+    size_t sk = gemm_prefill_scratch(T, 2 * E, dm, adt);
+    sk = std::max(sk, gemm_prefill_scratch(T, W, E, adt));
+    sk = std::max(sk, gemm_prefill_scratch(T, E, R, adt));
+    sk = std::max(sk, gemm_prefill_scratch(T, dm, E, adt));
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
     L.total = off;
@@ -178,9 +178,9 @@ DecodeWs decode_layout(const ssm_shard_desc_t* d, int64_t B, void* base) {
     const int64_t dm = d->d_model;
     size_t sk = 0;
     if (B > kFusedDecodeMax) {
-        sk = gemm_splitk_bytes(B, 2 * E, dm, adt, adt, kGemmInProj);
-        sk = std::max(sk, gemm_splitk_bytes(B, W, E, adt, adt, kGemmXProj));
-        sk = std::max(sk, gemm_splitk_bytes(B, dm, E, adt, adt, kGemmOutProj));
+        sk = gemm_decode_scratch(B, 2 * E, dm, adt, kGemmInProj);
+        sk = std::max(sk, gemm_decode_scratch(B, W, E, adt, kGemmXProj));
+        sk = std::max(sk, gemm_decode_scratch(B, dm, E, adt, kGemmOutProj));
     }
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
@@ -865,7 +865,11 @@ struct M2Ws {
     size_t total;
 };
 
-M2Ws m2_layout(const M2& m, int64_t T, int nseq, bool prefill, void* base) {
+// what a call needs of the workspace: all of it, the second prefill stage's part (a prefix of
+// it), or a decode step's
+enum M2Call { kM2Prefill, kM2PrefillStage2, kM2Decode };
+
+M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base) {
     M2Ws L{};
     char* b = (char*)base;
     size_t off = kWsHeader;
@@ -876,7 +880,7 @@ M2Ws m2_layout(const M2& m, int64_t T, int nseq, bool prefill, void* base) {
     L.g = take((size_t)T * m.E * 2);
     L.gn = take((size_t)T * m.E * 2);
     L.hs = (float*)take((size_t)T * m.H * 4);
-    if (prefill) {
+    if (call == kM2Prefill) {
         L.win = ssd_window_len(T, (int)m.H);
         L.maxw = ssd_max_windows(T, nseq, L.win);
         L.plan = take((size_t)L.maxw * 16);
@@ -884,8 +888,10 @@ M2Ws m2_layout(const M2& m, int64_t T, int nseq, bool prefill, void* base) {
         L.states = (float*)take(ssd_state_bytes(L.maxw, (int)m.H));
         L.lsum = (float*)take((size_t)L.maxw * m.H * 4);
     }
-    const size_t sk = std::max(gemm_splitk_bytes(T, m.rows, m.dm, SSM_BF16, SSM_BF16, kGemmInProj),
-                               gemm_splitk_bytes(T, m.dm, m.E, SSM_BF16, SSM_BF16, kGemmOutProj));
+    const size_t sk = call == kM2Decode ? std::max(gemm_decode_scratch(T, m.rows, m.dm, SSM_BF16, kGemmInProj),
+                                                   gemm_decode_scratch(T, m.dm, m.E, SSM_BF16, kGemmOutProj))
+                                        : std::max(gemm_prefill_scratch(T, m.rows, m.dm, SSM_BF16),
+                                                   gemm_prefill_scratch(T, m.dm, m.E, SSM_BF16));
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
     L.total = off;
@@ -948,7 +954,7 @@ int ssm2_shard_prefill_workspace_bytes(const ssm2_shard_desc_t* d, int64_t max_t
     SSM_TRY(m2_dims(d, &m));
     if (!bytes) return fail(SSM_E_INVAL, "bytes is null");
     if (max_tokens < 0 || max_seqs < 0) return fail(SSM_E_INVAL, "negative size");
-    *bytes = m2_layout(m, max_tokens, max_seqs, true, nullptr).total;
+    *bytes = m2_layout(m, max_tokens, max_seqs, kM2Prefill, nullptr).total;
     return SSM_OK;
 }
 
@@ -957,7 +963,7 @@ int ssm2_shard_decode_workspace_bytes(const ssm2_shard_desc_t* d, int32_t max_ba
     SSM_TRY(m2_dims(d, &m));
     if (!bytes) return fail(SSM_E_INVAL, "bytes is null");
     if (max_batch < 0) return fail(SSM_E_INVAL, "negative size");
-    *bytes = m2_layout(m, max_batch, 0, false, nullptr).total;
+    *bytes = m2_layout(m, max_batch, 0, kM2Decode, nullptr).total;
     return SSM_OK;
 }
 
@@ -1014,9 +1020,9 @@ int ssm2_shard_prefill_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weigh
     SSM_TRY(check_meta(meta, T));
     SSM_TRY(check_ptr(conv_pool, "conv_pool"));
     SSM_TRY(check_ptr(ssm_pool, "ssm_pool"));
-    M2Ws L = m2_layout(m, T, meta->nseq, true, nullptr);
+    M2Ws L = m2_layout(m, T, meta->nseq, kM2Prefill, nullptr);
     SSM_TRY(check_ws(ws, ws_bytes, L.total));
-    L = m2_layout(m, T, meta->nseq, true, ws);
+    L = m2_layout(m, T, meta->nseq, kM2Prefill, ws);
     if (meta->nseq == 0) return SSM_OK;
     if (T > 0) {
         SSM_TRY(check_ptr(x, "x"));
@@ -1056,9 +1062,9 @@ int ssm2_shard_prefill_stage2(const ssm2_shard_desc_t* d, const ssm2_shard_weigh
     SSM_TRY(check_ptr(sumsq, "sumsq"));
     SSM_TRY(check_ptr(y, "y_partial"));
     // the stage-1 part of the layout does not depend on the sequence count
-    M2Ws L = m2_layout(m, T, 0, false, nullptr);
+    M2Ws L = m2_layout(m, T, 0, kM2PrefillStage2, nullptr);
     SSM_TRY(check_ws(ws, ws_bytes, L.total));
-    L = m2_layout(m, T, 0, false, ws);
+    L = m2_layout(m, T, 0, kM2PrefillStage2, ws);
     return m2_stage2(m, w, sumsq, T, y, L, s, "m2.prefill.norm", "m2.prefill.out_proj");
 }
 
@@ -1069,9 +1075,9 @@ int ssm2_shard_decode_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weight
     SSM_TRY(m2_dims(d, &m));
     SSM_TRY(m2_check_weights(w));
     if (B < 0 || S <= 0) return fail(SSM_E_INVAL, "batch %d, num_slots %d", B, S);
-    M2Ws L = m2_layout(m, B, 0, false, nullptr);
+    M2Ws L = m2_layout(m, B, 0, kM2Decode, nullptr);
     SSM_TRY(check_ws(ws, ws_bytes, L.total));
-    L = m2_layout(m, B, 0, false, ws);
+    L = m2_layout(m, B, 0, kM2Decode, ws);
     if (B == 0) return SSM_OK;
     SSM_TRY(check_ptr(x, "x_t"));
     if (!slot) return fail(SSM_E_INVAL, "cache_slot is null");
@@ -1105,9 +1111,9 @@ int ssm2_shard_decode_stage2(const ssm2_shard_desc_t* d, const ssm2_shard_weight
     SSM_TRY(m2_dims(d, &m));
     SSM_TRY(m2_check_weights(w));
     if (B < 0) return fail(SSM_E_INVAL, "batch %d", B);
-    M2Ws L = m2_layout(m, B, 0, false, nullptr);
+    M2Ws L = m2_layout(m, B, 0, kM2Decode, nullptr);
     SSM_TRY(check_ws(ws, ws_bytes, L.total));
-    L = m2_layout(m, B, 0, false, ws);
+    L = m2_layout(m, B, 0, kM2Decode, ws);
     if (B == 0) return SSM_OK;
     SSM_TRY(check_ptr(sumsq, "sumsq"));
     SSM_TRY(check_ptr(y, "y_partial"));

@@ -676,14 +676,18 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
                    (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr);
         return hipGetLastError();
     }
-    SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, true, false, MB16, FINE, SB>), dim3(tm * tn, splits), dim3(64 * WM * WN), 0,
-               s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part);
-    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    KernelTimer kt("gemm.splitk_reduce", s);
-    const int64_t n = M * ((N + 3) / 4);
-    SSM_LAUNCH((splitk_reduce_kernel<CF>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const float*)part,
-               splits, (int)M, (int)N, C, ldc);
-    return hipGetLastError();
+    // K-slices are built for the tiles that pick_tile slices
+    if constexpr (BK == 64 && BM * BN <= 192 * 128 && BM != 96) {
+        SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, true, false, MB16, FINE, SB>), dim3(tm * tn, splits), dim3(64 * WM * WN), 0,
+                   s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part);
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        KernelTimer kt("gemm.splitk_reduce", s);
+        const int64_t n = M * ((N + 3) / 4);
+        SSM_LAUNCH((splitk_reduce_kernel<CF>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const float*)part,
+                   splits, (int)M, (int)N, C, ldc);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 // float32 operands on the DMA tiles: the rows are moved as bytes, so the kernel sees them as
@@ -709,26 +713,76 @@ hipError_t run_dma_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
     return hipGetLastError();
 }
 
-// Tile shape by a wave-quantisation cost model: whole rounds of 256 workgroups (one per
-// CU) times tile area over the shape's measured efficiency (256x256 does the most MFMA
-// work per LDS byte; 128x128 gives more workgroups when the grid is small). 256x320 (4x2
-// waves of 64x160) takes an output whose 256-wide tiles leave the last round part-empty
-// but whose N is a multiple of 320: out_proj of the 2.8B half shard (16384 x 2560) runs
-// 512 of them in 2 rounds instead of 640 256x256 tiles in 3. All three run on 16x16 blocks
-// with the second schedule (5-7% faster than 32x32 blocks with the first): 256x256 as 2x4
-// waves of 128x64, 128x128 as 2x2 waves of 64x64 (two workgroups per CU), 256x320 as 4x2
-// waves of 64x160 with one set of weight fragments (two sets do not fit in the registers).
-enum DmaTiles { kTiles128 = 0, kTiles256 = 1, kTiles256x320 = 2 };
-DmaTiles dma_tiles(int64_t M, int64_t N) {
-    auto cost = [&](int bm, int bn, double eff) {
-        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        return (double)((tiles + 255) / 256) * bm * bn / eff;
-    };
-    const double c256 = cost(256, 256, 1.0);
-    if (c256 > cost(128, 128, 0.83)) return kTiles128;
-    return (N % 320 == 0 && cost(256, 320, 1.0) < c256) ? kTiles256x320 : kTiles256;
+// bf16 tiles. Which one is fastest depends on how many of them the output gives: an MI355X
+// runs 256 workgroups at a time (one per CU; the two smallest tiles' rings fit a CU twice), and
+// a part-empty round costs as much as a full one. Every tile is therefore priced as
+//   launch + rounds x (a x (64-wide k-tiles) + b)
+// with a and b (us) fitted to its own measured times over 647 shapes, M = 80 .. 65536,
+// N = 80 .. 16384 and K = 384 .. 8192, weights read from memory; a is what a k-tile costs on a
+// CU that holds one tile (6.8 TFLOP/s per CU for 256x320, 4.4 for 128x128, 1.9 for 64x64: bytes
+// moved per flop), b the first loads' latency and the store. The cheapest is within 2% of the
+// best tile on average over those shapes (6% at the 90th percentile). Against the rule before
+// it (128x128 with a 2-deep ring, 256x256, 256x320 when N is a multiple of 320, and the decode
+// tile kernel up to 512 rows): 391x10240x2560 54.7 -> 30.9 us, 391x2560x5120 36.8 -> 25.3,
+// 1024x3584x3584 47.0 -> 32.9, 2048x2560x5120 85.0 -> 56.1, 2048x5120x2560 88.2 -> 52.0,
+// 4096x2560x5120 153.9 -> 94.3, 2900x4096x8192 202 -> 153, 65536x2560x5120 1303 -> 1223 us. A ring of 3 or 4 stages is worth more than a second workgroup
+// per CU on a grid that gives each CU one tile (128x128, 3-deep against 2-deep: 0.48 against
+// 0.75 us per k-tile).
+enum BfTile {
+    kT32x64, kT64x64, kT64x128, kT96x128, kT128x128, kT128x192, kT192x128, kT128x256, kT256x128, kT256x192, kT192x256,
+    kT256x256, kT256x320, kBfTiles
+};
+struct TileCost {
+    int bm, bn;
+    float a, a2, b;  // a2: per k-tile when two tiles share a CU (0: the ring fills it)
+    bool split;      // K-slices of it are built
+};
+constexpr TileCost kTileCost[kBfTiles] = {
+    {32, 64, 0.186f, 0.243f, 1.06f, true}, {64, 64, 0.278f, 0.381f, 0.84f, true}, {64, 128, 0.321f, 0.0f, 1.50f, true},
+    {96, 128, 0.405f, 0.0f, 2.55f, false}, {128, 128, 0.480f, 0.0f, 1.36f, true}, {128, 192, 0.633f, 0.0f, 2.48f, true},
+    {192, 128, 0.603f, 0.0f, 2.55f, true}, {128, 256, 0.786f, 0.0f, 2.74f, false}, {256, 128, 0.748f, 0.0f, 3.25f, false},
+    {256, 192, 1.087f, 0.0f, 2.76f, false}, {192, 256, 1.111f, 0.0f, 2.07f, false}, {256, 256, 1.336f, 0.0f, 3.01f, false},
+    {256, 320, 1.554f, 0.0f, 6.65f, false}};
+constexpr int kMaxSlices = 8, kMinSliceK = 8;  // K-slices: at most 8, of at least 8 k-tiles each
+constexpr float kLaunchUs = 2.0f;
+// K-slices write float32 partials, and a second kernel adds them (fitted on the same shapes)
+constexpr float kSplitUs = 3.8f, kSplitUsPerMB = 0.36f;
+
+struct GemmPlan {
+    int tile;    // BfTile, or -1: the few-row / decode tile kernels
+    int slices;  // K-slices (1: none)
+    float us;    // its price
+};
+
+// after a few rounds the workgroups no longer run in step: the last round costs about its share
+float rounds_of(int64_t wg) { return wg <= 4 * 256 ? (float)((wg + 255) / 256) : (float)wg / 256.0f + 0.6f; }
+
+float tile_us(const TileCost& t, int64_t wg, float nk) {
+    const float r = rounds_of(wg);
+    if (t.a2 > 0.0f && wg > 256) return kLaunchUs + (float)((wg + 511) / 512) * t.a2 * nk + r * t.b;
+    return kLaunchUs + r * (t.a * nk + t.b);
 }
-bool dma_big_tiles(int64_t M, int64_t N) { return dma_tiles(M, N) != kTiles128; }
+
+// the cheapest tile (and K-slice count within the scratch) for C[M][N] = A[M][K] B[N][K]^T,
+// K a multiple of 64
+GemmPlan pick_tile(int64_t M, int64_t N, int64_t K, size_t scratch_bytes) {
+    GemmPlan best{kT64x64, 1, 1e30f};
+    const int64_t nk = K / 64;
+    for (int i = 0; i < kBfTiles; ++i) {
+        const TileCost& t = kTileCost[i];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        const float u = tile_us(t, tiles, (float)nk);
+        if (u < best.us) best = GemmPlan{i, 1, u};
+        if (!t.split || tiles >= 192) continue;
+        for (int d = 2; d <= kMaxSlices && d * kMinSliceK <= nk && tiles * d <= 288; ++d) {
+            const size_t bytes = (size_t)d * M * N * 4;
+            if (nk % d != 0 || bytes > scratch_bytes) continue;
+            const float us = tile_us(t, tiles * d, (float)(nk / d)) + kSplitUs + kSplitUsPerMB * (float)bytes * 1e-6f;
+            if (us < best.us) best = GemmPlan{i, d, us};
+        }
+    }
+    return best;
+}
 
 // Float32 tiles by the same kind of model: rounds of workgroups (one per CU; two for the 64 KB
 // ring of 128x128) times the work a CU does per round over the tile's measured per-CU MFMA
@@ -760,43 +814,83 @@ F32Tiles f32_tiles(int64_t M, int64_t N) {
 bool decode_tiles(int64_t M, int64_t N, int64_t K) {
     return K % 64 == 0 && M > 64 && M <= 512 && ((M + 31) / 32) * ((N + 31) / 32) >= 128;
 }
-// x_proj of a decode batch (up to 512 rows, at most 256 columns): 16-row tiles of the
-// few-row kernel, which spread over more workgroups than 64-row tiles and need no K-slices
-bool xproj_decode_skinny(int64_t M, int64_t N) { return M <= 512 && N <= 256; }
-
-// Split-K for outputs of fewer tiles than CUs: K is cut into equal slices of whole
-// 64-wide k-tiles (at least two per slice) so that up to ~384 workgroups run; the slices'
-// fp32 partials are added by a reduce kernel in slice order (deterministic).
-int splitk_slices(int64_t tiles, int64_t K) {
-    if (K % 64 != 0 || tiles >= 256) return 1;
-    const int64_t nk = K / 64, cap = std::max<int64_t>(1, 384 / tiles);
-    int best = 1;
-    for (int64_t d = 2; d <= cap && d <= nk / 2; ++d)
-        if (nk % d == 0) best = (int)d;
-    return best;
+// ... and its price in pick_tile's terms: the tile that launch_dtile_pick takes, fitted on the
+// same shapes (64x64: 104 shapes within 7%). It wins up to about 256 rows over outputs that
+// give one round of its tiles (80x2560x2560 9.1 us against 11.0 on the DMA tiles, 200x3584x3584
+// 15.4 against 17.1; 391x2560x2560 19.2 against 15.9).
+float decode_tile_us(int64_t M, int64_t N, int64_t K) {
+    const int64_t tm64 = (M + 63) / 64, tm32 = (M + 31) / 32, tn64 = (N + 63) / 64, tn32 = (N + 31) / 32;
+    const float nk = (float)(K / 64);
+    if (M > 128 && tm64 * tn64 >= 128) return 1.7f + rounds_of(tm64 * tn64) * (1.83f + 0.218f * nk);
+    if (tm64 * tn32 >= 128) return 0.7f + rounds_of(tm64 * tn32) * (2.03f + 0.169f * nk);
+    return 1.8f + rounds_of(tm32 * tn32) * (1.82f + 0.066f * nk);
+}
+// x_proj of up to 512 rows (at most 512 columns): 16-row tiles of the few-row kernel, which
+// spread over more workgroups than the DMA tiles and need no K-slices. Every wave streams its
+// share of K for one 16x16 tile: 192 columns, K = 1280 / 2560 / 5120 at 256 rows 4.6 / 6.9 /
+// 11.7 us (DMA tiles 6.6 / 8.3 / 10.2), at 391 rows (a second round) 7.2 / 11.4 / 20.7
+// (6.6 / 8.5 / 10.3).
+bool xproj_decode_skinny(int64_t M, int64_t N) { return M <= 512 && N <= 512; }
+float xproj_skinny_us(int64_t M, int64_t N, int64_t K) {
+    return 2.0f + rounds_of(((M + 15) / 16) * ((N + 15) / 16)) * 0.122f * (float)(K / 64);
 }
 
-int fit_slices(int sp, int64_t M, int64_t N, size_t scratch_bytes) {
-    return (sp > 1 && (size_t)sp * M * N * 4 <= scratch_bytes) ? sp : 1;
+template <bool CF> GemmPlan plan_bf16(GemmRole role, int64_t M, int64_t N, int64_t K, size_t scratch_bytes) {
+    GemmPlan p = pick_tile(M, N, K, scratch_bytes);
+    float few = 1e30f;
+    if (CF && role == kGemmXProj && xproj_decode_skinny(M, N)) few = xproj_skinny_us(M, N, K);
+    if (!CF && decode_tiles(M, N, K)) few = decode_tile_us(M, N, K);
+    if (few < p.us) p = GemmPlan{-1, 1, few};
+    return p;
 }
 
 template <int ROLE, bool CF>
-hipError_t dispatch_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
-                        void* C, int64_t ldc, hipStream_t s, float* scratch, size_t scratch_bytes) {
-    if (K % 64 == 0) {
-        const DmaTiles t = dma_tiles(M, N);
-        if (t == kTiles256x320)
-            return run_dma<ROLE, 256, 320, 64, 2, 4, 2, CF, true, true, true>(M, N, K, A, lda, B, ldb, C, ldc, s);
-        if (t == kTiles256) return run_dma<ROLE, 256, 256, 64, 2, 2, 4, CF, true, true>(M, N, K, A, lda, B, ldb, C, ldc, s);
+hipError_t dispatch_dma(const GemmPlan& g, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
+                        int64_t ldb, void* C, int64_t ldc, hipStream_t s, float* scratch) {
+#define SSM_TILE(T, BM, BN, NS, WM, WN, SB)                                                                  \
+    case T: return run_dma<ROLE, BM, BN, 64, NS, WM, WN, CF, true, true, SB>(M, N, K, A, lda, B, ldb, C, ldc, s, \
+                                                                             g.slices, scratch)
+    switch (g.tile) {
+        SSM_TILE(kT32x64, 32, 64, 6, 1, 4, false);
+        SSM_TILE(kT64x64, 64, 64, 4, 2, 2, false);
+        SSM_TILE(kT64x128, 64, 128, 4, 2, 4, false);
+        SSM_TILE(kT96x128, 96, 128, 4, 2, 2, false);
+        SSM_TILE(kT128x128, 128, 128, 3, 2, 4, false);
+        SSM_TILE(kT128x192, 128, 192, 3, 2, 4, false);
+        SSM_TILE(kT192x128, 192, 128, 3, 2, 4, false);
+        SSM_TILE(kT128x256, 128, 256, 3, 2, 4, false);
+        SSM_TILE(kT256x128, 256, 128, 3, 4, 2, false);
+        SSM_TILE(kT256x192, 256, 192, 2, 4, 2, false);
+        SSM_TILE(kT192x256, 192, 256, 2, 2, 4, false);
+        SSM_TILE(kT256x256, 256, 256, 2, 2, 4, false);
+        // one set of weight fragments: two sets of its 64x160 wave tiles do not fit the registers
+        SSM_TILE(kT256x320, 256, 320, 2, 4, 2, true);
     }
-    if (K % 64 == 0) {
-        const int sp = fit_slices(splitk_slices(((M + 127) / 128) * ((N + 127) / 128), K), M, N, scratch_bytes);
-        return run_dma<ROLE, 128, 128, 64, 2, 2, 2, CF, true, true>(M, N, K, A, lda, B, ldb, C, ldc, s, sp, scratch);
-    }
-    // K a multiple of 32 only (dt_proj: K = dt_rank): a 3-slot ring (48 KB) lets three
-    // workgroups share a CU, which shortens the many short-lived tiles' latency rounds
-    // (dt_proj of 16384 tokens, K = 160: 35 -> 30 us against a 4-slot ring)
-    return run_dma<ROLE, 128, 128, 32, 3, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+#undef SSM_TILE
+    return hipErrorInvalidValue;
+}
+
+// K a multiple of 32 only, or a K of few 64-wide tiles (dt_proj: K = dt_rank): 32-wide stages,
+// whose rings stay small enough for several workgroups per CU; the many short-lived tiles hide
+// each other's first loads. 64x64 tiles while they fit two rounds (256x3584x224 5.9 -> 4.1 us,
+// 256x2560x160 5.2 -> 3.6), 256x128 ones once they fill four rounds (16384x8192x256 103 -> 96,
+// 65536x2560x160 129 -> 113, 65536x3584x224 205 -> 176 us against 128x128 with a 3-deep ring),
+// 128x128 between (2048x3584x224 9.9 -> 9.1).
+template <int ROLE, bool CF>
+hipError_t dispatch_dma32(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
+                          void* C, int64_t ldc, hipStream_t s) {
+    if (((M + 63) / 64) * ((N + 63) / 64) <= 512)
+        return run_dma<ROLE, 64, 64, 32, 4, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    if (((M + 255) / 256) * ((N + 127) / 128) >= 1024)
+        return run_dma<ROLE, 256, 128, 32, 3, 4, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    return run_dma<ROLE, 128, 128, 32, 4, 2, 4, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+}
+
+// Scratch that a product may use for K-slices in a prefill of up to M rows: what kMaxSlices
+// slices need, up to what the largest grid of K-slices (288 tiles of 192x128) holds.
+// Monotone in M, so a workspace for more rows serves fewer.
+size_t splitk_reserve(int64_t M, int64_t N) {
+    return M <= 64 ? 0 : std::min((size_t)kMaxSlices * M * N * 4, (size_t)288 * 192 * 128 * 4);
 }
 
 // fp32 weights and at most 8 activation rows (a decode step of the fp32 configuration),
@@ -939,6 +1033,10 @@ int f32_slices(int64_t tiles, int64_t K) {
     return best;
 }
 
+int fit_slices(int sp, int64_t M, int64_t N, size_t scratch_bytes) {
+    return (sp > 1 && (size_t)sp * M * N * 4 <= scratch_bytes) ? sp : 1;
+}
+
 template <int ROLE, int BM, int BN, int WM, int WN, bool AF, bool CF>
 hipError_t run_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                     void* C, int64_t ldc, hipStream_t s) {
@@ -963,30 +1061,24 @@ __global__ __launch_bounds__(256) void round_bf16_rows_kernel(const float* __res
 template <int ROLE, bool AF, bool CF>
 hipError_t dispatch_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                          void* C, int64_t ldc, hipStream_t s, float* scratch, size_t scratch_bytes) {
-    // Tile by output size: large outputs use 256x256 (each wave 128x128, the most
-    // MFMA work per LDS byte), mid-size ones 128x128 for more workgroups.
-    // few rows: the weight read dominates; stream it with many narrow workgroups. fp32-A
-    // dt_proj of a large decode batch (K = dt_rank) goes the same way: its staged 128x128
-    // tiles would give only a few workgroups (20 for 256 sequences of a 1280-channel shard)
-    if (M <= 64 || (ROLE == kGemmDtProj && AF && M <= 512 && K <= 512) ||
-        (ROLE == kGemmXProj && !AF && xproj_decode_skinny(M, N)) || (!AF && !CF && decode_tiles(M, N, K))) {
+    auto few_rows = [&]() {
         SkinnyArgs p{};
         p.A = A; p.lda = lda; p.a_f32 = AF; p.B = (const bf16*)B; p.ldb = ldb; p.C = C; p.ldc = ldc;
         p.M = (int)M; p.N = (int)N; p.K = (int)K;
         return launch_gemm_skinny(p, CF ? kSkinnyStoreF32 : kSkinnyStoreBf16, s);
-    }
-    if constexpr (ROLE == kGemmXProj && !AF) {
-        // x_proj: few output columns (R + 2N), long K; one 64-row tile spans all of N so
-        // that every activation row is read once, with a 3-deep ring to cover the latency
-        // that four waves per CU leave exposed
-        if (K % 64 == 0 && N <= 256) {
-            const int sp = fit_slices(splitk_slices((M + 63) / 64, K), M, N, scratch_bytes);
-            if (N <= 192) return run_dma<ROLE, 64, 192, 64, 3, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s, sp, scratch);
-            return run_dma<ROLE, 64, 256, 64, 3, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s, sp, scratch);
-        }
-    }
+    };
+    // few rows: the weight read dominates; stream it with many narrow workgroups. fp32-A
+    // dt_proj of a large decode batch (K = dt_rank) goes the same way: its staged 128x128
+    // tiles would give only a few workgroups (20 for 256 sequences of a 1280-channel shard)
+    if (M <= 64 || (ROLE == kGemmDtProj && AF && M <= 512 && K <= 512)) return few_rows();
     if constexpr (!AF) {
-        if (K % 32 == 0) return dispatch_dma<ROLE, CF>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
+        if (K % 64 == 0 && !(ROLE == kGemmDtProj && K <= 256)) {
+            const GemmPlan g = plan_bf16<CF>((GemmRole)ROLE, M, N, K, scratch ? scratch_bytes : 0);
+            if (g.tile < 0) return few_rows();
+            return dispatch_dma<ROLE, CF>(g, M, N, K, A, lda, B, ldb, C, ldc, s, scratch);
+        }
+        if (ROLE == kGemmXProj && xproj_decode_skinny(M, N)) return few_rows();
+        if (K % 32 == 0) return dispatch_dma32<ROLE, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
     }
     // staged path: fp32 A (rounded while staging) or a K tail; short K favours more tiles
     const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
@@ -1003,23 +1095,56 @@ hipError_t launch_round_bf16_rows(const float* a, int64_t lda, void* o, int64_t 
     return hipGetLastError();
 }
 
-size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role) {
+namespace {
+size_t f32_splitk_bytes(int64_t M, int64_t N, int64_t K) {
     // float32 operands on 128x128 tiles (more than the 64 rows of the streamed kernel)
-    if (a_dt == SSM_F32 && b_dt == SSM_F32) {
-        if (M <= 64 || N == 0 || f32_slices(((M + 127) / 128) * ((N + 127) / 128), K) <= 1) return 0;
-        const int sp = f32_slices(((M + 63) / 64) * ((N + 63) / 64), K);
-        return sp > 1 ? (size_t)sp * M * N * 4 : 0;
-    }
-    // mirrors the dispatch below: the DMA paths with bf16 operands and K % 64 == 0
-    if (M <= 64 || N == 0 || b_dt != SSM_BF16 || a_dt != SSM_BF16 || K % 64 != 0) return 0;
-    int64_t tiles;
-    if (role == kGemmXProj && xproj_decode_skinny(M, N)) return 0;
-    if (decode_tiles(M, N, K) && role != kGemmXProj) return 0;
-    if (role == kGemmXProj && N <= 256) tiles = (M + 63) / 64;
-    else if (dma_big_tiles(M, N)) return 0;
-    else tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const int sp = splitk_slices(tiles, K);
+    if (M <= 64 || N == 0 || f32_slices(((M + 127) / 128) * ((N + 127) / 128), K) <= 1) return 0;
+    const int sp = f32_slices(((M + 63) / 64) * ((N + 63) / 64), K);
     return sp > 1 ? (size_t)sp * M * N * 4 : 0;
+}
+}  // namespace
+
+size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role) {
+    if (a_dt == SSM_F32 && b_dt == SSM_F32) return f32_splitk_bytes(M, N, K);
+    if (M <= 64 || N == 0 || b_dt != SSM_BF16 || a_dt != SSM_BF16 || K % 64 != 0) return 0;
+    if (role == kGemmXProj && M <= 512 && N <= 256) return 0;  // few-row kernel or whole tiles
+    // the most that a choice of pick_tile's can use
+    int most = 1;
+    const int64_t nk = K / 64;
+    for (const TileCost& t : kTileCost) {
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (!t.split || tiles >= 192) continue;
+        for (int d = 2; d <= kMaxSlices && d * kMinSliceK <= nk && tiles * d <= 288; ++d)
+            if (nk % d == 0) most = std::max(most, d);
+    }
+    return most > 1 ? (size_t)most * M * N * 4 : 0;
+}
+
+size_t gemm_prefill_scratch(int64_t M, int64_t N, int64_t K, int dt) {
+    if (dt == SSM_F32) return f32_splitk_bytes(M, N, K);
+    return K % 64 == 0 ? splitk_reserve(M, N) : 0;
+}
+
+// The decode workspace's K-slice scratch: none where the few-row kernels or the decode tiles
+// run unsliced (every batch up to 512 over outputs of 128 of their tiles); else what up to 384
+// workgroups of 128x128 tiles would use, which pick_tile may spend on any tile.
+size_t gemm_decode_scratch(int64_t M, int64_t N, int64_t K, int dt, GemmRole role) {
+    if (dt == SSM_F32) return f32_splitk_bytes(M, N, K);
+    if (M <= 64 || N == 0 || K % 64 != 0) return 0;
+    if (role == kGemmXProj ? M <= 512 && N <= 256 : decode_tiles(M, N, K)) return 0;
+    auto cost = [&](int t, double eff) {
+        const int64_t n = ((M + t - 1) / t) * ((N + t - 1) / t);
+        return (double)((n + 255) / 256) * t * t / eff;
+    };
+    int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    if (role == kGemmXProj && N <= 256) tiles = (M + 63) / 64;
+    else if (cost(256, 1.0) <= cost(128, 0.83)) return 0;
+    if (tiles >= 256) return 0;
+    const int64_t nk = K / 64, cap = std::max<int64_t>(1, 384 / tiles);
+    int best = 1;
+    for (int64_t d = 2; d <= cap && d <= nk / 2; ++d)
+        if (nk % d == 0) best = (int)d;
+    return best > 1 ? (size_t)best * M * N * 4 : 0;
 }
 
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt, const void* B,
@@ -1123,8 +1248,9 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
     }
     if (af && cf) return dispatch_bf16<kGemmGeneric, true, true>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
     if (af) return dispatch_bf16<kGemmGeneric, true, false>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
-    if (cf) return dispatch_bf16<kGemmGeneric, false, true>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
-    return dispatch_bf16<kGemmGeneric, false, false>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
+    // bf16 operands: the instances of the projections with this output type
+    if (cf) return dispatch_bf16<kGemmXProj, false, true>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
+    return dispatch_bf16<kGemmInProj, false, false>(M, N, K, A, lda, B, ldb, C, ldc, s, scratch, scratch_bytes);
 }
 
 }  // namespace ssm

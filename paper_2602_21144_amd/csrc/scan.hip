@@ -25,7 +25,7 @@ namespace ssm {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kMinWin = 32, kMaxWin = 2048;
+constexpr int kShortWin = 32, kMaxWin = 2048;
 constexpr int kTargetWaves = 3072;  // 3 per SIMD: the main pass holds 156 VGPRs per lane
 
 // flags per window, written by pass A
@@ -704,10 +704,28 @@ __global__ __launch_bounds__(256) void decode_dt_ssm_kernel(ScanArgs a) {
 // runs the same number of waves (the main pass fits 3 per SIMD). Any multiple of the
 // token block works; rounding to a power of two instead left the busiest SIMDs a fifth
 // more work than the average (2560 waves on 1024 SIMDs for the 2.8B half shard).
+// Short batches, whose windows would come out shorter than 32 tokens: the passes are then a
+// start of ~3 us and a serial walk of one window, the link pass grows with the window count,
+// and the length is the one whose sum is least. us per token of a window at w waves per SIMD,
+// as measured: 0.31 up to one wave, 0.37 just above, 0.50, 0.56 at two, 0.75 up to three. The
+// three passes together, windows of 32 tokens against this rule: 64 and 128 tokens of a 5120-channel
+// layer 31.3 -> 16.7 and 20.5 us, 391 tokens 34.1 -> 32.2, 256 tokens of 640 channels
+// 29.0 -> 14.9, 256 float32 tokens of 1536 channels 30.7 -> 16.6 us.
 int scan_window_len(int64_t T, int E) {
     const int64_t tw = target_windows(E);
     const int64_t want = ((T + tw - 1) / tw + kTB - 1) / kTB * kTB;
-    return (int)std::min<int64_t>(kMaxWin, std::max<int64_t>(kMinWin, want));
+    if (want >= kShortWin) return (int)std::min<int64_t>(kMaxWin, want);
+    int best = kShortWin;
+    float best_us = 1e30f;
+    for (int win = (int)std::max<int64_t>(want, kTB); win <= kShortWin; win += kTB) {
+        const int64_t nw = (T + win - 1) / win;  // at most tw, which the scratch is sized for
+        const float w = (float)(nw * (E / kWave)) / 1024.0f;
+        const float tok = w <= 1.0f ? 0.31f : w <= 1.05f ? 0.37f : w <= 1.5f ? 0.50f : w <= 2.0f ? 0.56f : 0.75f;
+        const float link = 0.2f * (float)((nw + 7) / 8) + (float)(nw * E) * (128.0f / 15e6f);
+        const float us = 2.0f * (float)win * tok + link;
+        if (us < best_us) { best_us = us; best = win; }
+    }
+    return best;
 }
 
 static int64_t max_windows(int64_t max_T, int E) {

@@ -363,6 +363,15 @@ def test_selective_scan(B, act, E, lens):
 
 
 @pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("E,lens", [(2560, [500, 3, 9]), (1280, [700, 0, 1, 1290]), (384, [4000, 77, 19])])
+def test_selective_scan_short_windows(B, act, E, lens):
+    """Batches whose windows come out shorter than 32 tokens (8, 16 and 24 here): sequences over
+    many windows, several sequences in one window, ends on and off window boundaries. The
+    tolerances are those of the longer windows: the same recurrence, linked more often."""
+    test_selective_scan(B, act, E, lens)
+
+
+@pytest.mark.parametrize("act", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [3333, 9001])
 def test_selective_scan_long_sequence_many_windows(B, act, T):
     """One long sequence crossing ~100 (~280) windows: exercises the window-to-window state

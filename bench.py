@@ -38,6 +38,9 @@ if ROOT not in sys.path:
 METRIC = "selective-scan prefill tokens/s + decode µs/step per shard; % HBM/MFMA peak"
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}     # dense MFMA
+# float32 products of prefill size run as three f16 products on operands held as sums of two f16
+# values: their roof, in float32 flops, is a third of the dense f16 peak
+PEAK_F32_HALVES_TFLOPS = 2500.0 / 3
 # VALU issue: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles, 2.4 GHz
 PEAK_VALU_GINSTS = 256 * 4 * 2.4e9 / 4 / 1e9
 
@@ -136,13 +139,14 @@ def kernel_work(sh, kind, n, nseq):
     bf = sh.act == "bf16"
     if kind == "prefill":
         T = n
-        out = {"prefill.in_proj": ("mfma", 2.0 * T * 2 * E * dm),
+        mfma = "mfma" if bf or T <= 64 else "mfma_halves"
+        out = {"prefill.in_proj": (mfma, 2.0 * T * 2 * E * dm),
                "prefill.conv1d": ("hbm", 2 * T * E * s + E * (K + 1) * s),
                "prefill.conv_history": ("hbm", 2 * nseq * E * (K - 1) * s),
                "prefill.x_proj": ("hbm", T * E * s + W * E * s + T * W * 4),
                "prefill.dt_proj": ("hbm", T * R * s + E * R * s + T * E * s),
                "prefill.scan": ("hbm", 4 * T * E * s + T * 2 * N * 4 + 2 * nseq * E * N * 4 + E * (N + 2) * 4),
-               "prefill.out_proj": ("mfma", 2.0 * T * dm * E)}
+               "prefill.out_proj": (mfma, 2.0 * T * dm * E)}
         if bf and R % 32 == 0 and T > 64:
             out["prefill.dt_round"] = ("hbm", T * R * 4 + T * R * 2)
         return out
@@ -188,6 +192,11 @@ def keep_busy(torch, ms=1.0):
     every sampled dispatch behind queued work."""
     if hasattr(torch.cuda, "_sleep"):
         torch.cuda._sleep(int(ms * 2.0e6))
+
+
+def mfma_peak(roof, act):
+    """TFLOP/s of the matrix cores for a roof, None when it is not theirs."""
+    return {"mfma": PEAK_TFLOPS[act], "mfma_halves": PEAK_F32_HALVES_TFLOPS}.get(roof)
 
 
 def role_of(name):
@@ -375,7 +384,8 @@ def measure(B, torch, wl, steps, warmup, dominant_every=None):
     sampled = B.ssm_timing_collect()
     per_step = launches_per_step(wl)
     # per kernel name: (launches per step, average ms of its sampled launches)
-    breakdown = {k: (per_step.get(k, n), ms / n) for k, (n, ms) in sampled.items()}
+    # (names outside kernel_work: about 16 launches for every one sampled)
+    breakdown = {k: (per_step.get(k, 16 * n), ms / n) for k, (n, ms) in sampled.items()}
     dominant = max(breakdown, key=lambda k: breakdown[k][0] * breakdown[k][1])
     dom_avg_ms = breakdown[dominant][1]
     every = dominant_every or (1 if dom_avg_ms >= 0.2 else 16)
@@ -420,7 +430,6 @@ def kernel_figures(wl, m):
     sh = wl.sh
     bd = m["breakdown"]
     total = sum(n * ms for n, ms in bd.values())
-    mf_peak = PEAK_TFLOPS[sh.act]
     out = {}
     for name, (n, ms) in sorted(bd.items(), key=lambda kv: -kv[1][0] * kv[1][1]):
         e = {"launches": n, "avg_us": round(1e3 * ms, 3), "share_of_step": round(n * ms / total, 4)}
@@ -429,8 +438,9 @@ def kernel_figures(wl, m):
             roof, amts = m["work"][role]
             sampled = amts[::16]
             rate = (sum(sampled) / len(sampled)) / (ms * 1e-3)
-            if roof == "mfma":
-                e.update(bound="mfma", achieved=round(rate / 1e12, 2), unit="TFLOP/s", peak=mf_peak,
+            mf_peak = mfma_peak(roof, sh.act)
+            if mf_peak:
+                e.update(bound=roof, achieved=round(rate / 1e12, 2), unit="TFLOP/s", peak=round(mf_peak, 1),
                          frac=round(rate / 1e12 / mf_peak, 4))
             else:
                 e.update(bound="hbm", achieved=round(rate / 1e9, 1), unit="GB/s", peak=PEAK_HBM_GBS,
@@ -474,8 +484,8 @@ def roofline_entry(wl, m):
     if m["sampled_work"] is not None:
         rate = m["sampled_work"] / (m["dom_ms"] * 1e-3)
         per_launch = m["sampled_work"] / m["dom_launches"]
-        if roof == "mfma":
-            ach, peak, unit = rate / 1e12, PEAK_TFLOPS[sh.act], "TFLOP/s"
+        if mfma_peak(roof, sh.act):
+            ach, peak, unit = rate / 1e12, mfma_peak(roof, sh.act), "TFLOP/s"
         else:
             ach, peak, unit = rate / 1e9, PEAK_HBM_GBS, "GB/s"
     tr = profile_counters(profile_stem(wl.key, sh.act), "traffic", dom)

@@ -248,9 +248,10 @@ int ssm_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int
  * generic, 1 in_proj, 2 x_proj, 3 dt_proj, 4 out_proj), as the prefill runs it. Outputs
  * with fewer tiles than the GPU has compute units and a long K may be computed split-K: the
  * K-slices' float32 partials go to scratch (device, the caller's; ssm_gemm_splitk_bytes
- * gives the most that the shape can use, 0 when it is never split) and a second kernel adds
- * them in slice order. With less scratch than that the product runs in fewer slices, with
- * none unsplit. */
+ * gives the most that the shape can use, 0 when it uses none) and a second kernel adds
+ * them in slice order. Float32 products of prefill size may keep their operands there as sums
+ * of f16 halves (no less exact than the float32 tiles). With less scratch than that the product
+ * runs in fewer slices or on float32 operands, with none unsplit. */
 int ssm_gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int32_t a_dtype, int32_t b_dtype, int32_t role,
                           size_t* bytes);
 int ssm_gemm_nt_role(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int32_t a_dtype, const void* B,

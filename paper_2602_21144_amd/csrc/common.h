@@ -174,7 +174,12 @@ hipError_t launch_round_bf16_rows(const float* a, int64_t lda, void* o, int64_t 
 // scratch the GEMM runs in fewer slices or unsplit.
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt,
                           const void* B, int64_t ldb, int b_dt, void* C, int64_t ldc, int c_dt,
-                          hipStream_t s, GemmRole role, float* scratch = nullptr, size_t scratch_bytes = 0);
+                          hipStream_t s, GemmRole role, float* scratch = nullptr, size_t scratch_bytes = 0,
+                          void* halves = nullptr, size_t halves_bytes = 0);
+// halves: room for float32 operands as f16 halves (gemm_split.hip), on which a large float32
+// product runs several times faster; gemm_f32_halves_bytes gives the size (monotone in M, 0:
+// never run this way), and with less the product runs on float32 operands.
+size_t gemm_f32_halves_bytes(int64_t M, int64_t N, int64_t K);
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role);
 // the K-slice scratch that a prefill of up to M rows (monotone in M for bf16) and a decode batch
 // of M reserve for such a product (operands of type dt)

@@ -9,7 +9,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "common.h"
+#include "gemm_tiles.h"
 
 namespace ssm {
 namespace {
@@ -19,25 +19,6 @@ constexpr int kBK = 64;  // k per LDS stage (bf16): 128 bytes per row = 8 chunks
 // Row r of an LDS tile stores its 8 chunks permuted by an XOR with (r>>1)&7, so the
 // 16 lanes that read one chunk column from 16 consecutive rows hit distinct banks.
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
-
-// Map the linear workgroup id to an output tile. Workgroups are dispatched round robin
-// over the 8 XCDs; regroup so each XCD gets a contiguous run of tiles, and order the
-// tiles in groups of 4 tile-rows so that a run shares A panels and B panels in its L2
-// (groups of 4 took dt_proj's 2560 short tiles from 31 to 28 us; 8 and 16 measured the
-// same or slower on every projection).
-__device__ __forceinline__ void tile_of(int tiles_m, int tiles_n, int& tm, int& tn) {
-    int nwg = gridDim.x;
-    int bid = blockIdx.x;
-    if ((nwg & 7) == 0) bid = (bid & 7) * (nwg >> 3) + (bid >> 3);
-    constexpr int G = 4;
-    int per_group = G * tiles_n;
-    int grp = bid / per_group;
-    int first = grp * G;
-    int gm = min(tiles_m - first, G);
-    int r = bid - grp * per_group;
-    tm = first + r % gm;
-    tn = r / gm;
-}
 
 __device__ __forceinline__ bf16x8 cvt8(float4 a, float4 b) {
     bf16x8 o;
@@ -184,15 +165,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt(int M, int N, int K,
     }
 }
 
-// f(integral_constant<int, i>) for i = 0 .. N-1, unrolled at compile time
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
-    static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
 // bf16 operands, K a multiple of BK: tiles move global -> LDS on the DMA path
 // (buffer_load_dwordx4 ... lds: each lane writes 16 bytes at its lane slot of a 1 KB LDS
 // block), so there are no staging registers and no ds_write instructions. A lane picks
@@ -203,13 +175,6 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
 // compiler does not serialise the prefetch behind each tile's LDS reads. Rows past M
 // or N are clamped to a valid row (their results are never stored). Fragments of
 // k-substep s+1 are read from LDS while the MFMAs of substep s run.
-// chunk permutation of an LDS row: 16 lanes reading one chunk column of 16 consecutive
-// rows hit distinct 16-byte bank groups (128-byte rows: key (r>>1)&7; 64-byte: (r>>2)&3)
-template <int BK> __device__ __forceinline__ int swz_k(int row, int chunk) {
-    if constexpr (BK == 64) return chunk ^ ((row >> 1) & 7);
-    else return chunk ^ ((row >> 2) & 3);
-}
-
 // WM x WN waves; with 8 waves two share each SIMD, so one wave's barrier and LDS waits
 // are covered by the other's MFMAs. SPLIT: workgroup (tile, blockIdx.y) multiplies the
 // K-slice [blockIdx.y * K, (blockIdx.y + 1) * K) (K is the slice length) and stores its
@@ -217,6 +182,9 @@ template <int BK> __device__ __forceinline__ int swz_k(int row, int chunk) {
 // F32: the operands are float32 rows passed as bf16 rows of twice the length (K, lda and
 // ldb in bf16 units); the DMA and the LDS layout only move bytes, and each 16-byte fragment
 // (4 floats along k) feeds four v_mfma_f32_32x32x2_f32 instead of one bf16 MFMA.
+// ea, eb (F32 only, may be null): the rows' and columns' exponents of the split product launched
+// before (gemm_split.hip); only the outputs of marked rows and columns are computed here, and a
+// tile without any returns at once.
 // MB16: 16x16 MFMA blocks. FINE: the second, fully ordered schedule of the k loop. SB (with
 // FINE): one set of weight fragments, each reloaded right after its last MFMA of a substep
 // (the MFMAs run weight block by weight block), which frees registers for wider tiles.
@@ -225,7 +193,9 @@ template <int ROLE, int BM, int BN, int BK, int NS, int WM, int WN, bool C_F32, 
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int K, const bf16* __restrict__ A,
                                                               int64_t lda, const bf16* __restrict__ B, int64_t ldb,
                                                               void* __restrict__ Cp, int64_t ldc, int tiles_m,
-                                                              int tiles_n, float* __restrict__ part) {
+                                                              int tiles_n, float* __restrict__ part,
+                                                              const int32_t* __restrict__ ea = nullptr,
+                                                              const int32_t* __restrict__ eb = nullptr) {
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     // MFMA blocks: 32x32 (bf16 32x32x16 or fp32 32x32x2), or 16x16 (MB16: bf16 16x16x32 or
@@ -268,6 +238,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int 
     const int m0 = tm * BM, n0 = tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
+    if constexpr (F32 && !SPLIT) {
+        if (ea) {
+            bool marked = false;
+            for (int r = tid; r < BM; r += 64 * NW) marked = marked || (m0 + r < M && ea[m0 + r] == kSplitBad);
+            for (int r = tid; r < BN; r += 64 * NW) marked = marked || (n0 + r < N && eb[n0 + r] == kSplitBad);
+            if (!__syncthreads_or(marked)) return;
+        }
+    }
     if constexpr (SPLIT) {
         A += (int64_t)blockIdx.y * K;
         B += (int64_t)blockIdx.y * K;
@@ -575,6 +553,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int 
                 if (m >= M || n >= N) continue;
                 const OT* q = st + r * BN + ((cc ^ (r & 7)) * E16);
                 OT* p = out + (int64_t)m * ldo + n;
+                if constexpr (F32 && !SPLIT) {
+                    if (ea) {
+                        const bool row = ea[m] == kSplitBad;
+                        for (int e = 0; e < E16 && n + e < N; ++e)
+                            if (row || eb[n + e] == kSplitBad) p[e] = q[e];
+                        continue;
+                    }
+                }
                 if (vec && n + E16 <= N) {
                     *(u32x4*)p = *(const u32x4*)q;
                 } else {
@@ -673,13 +659,14 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
     const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
     if (splits <= 1) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, false, false, MB16, FINE, SB>), dim3(tm * tn), dim3(64 * WM * WN), 0, s,
-                   (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr);
+                   (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr, nullptr, nullptr);
         return hipGetLastError();
     }
     // K-slices are built for the tiles that pick_tile slices
     if constexpr (BK == 64 && BM * BN <= 192 * 128 && BM != 96) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, true, false, MB16, FINE, SB>), dim3(tm * tn, splits), dim3(64 * WM * WN), 0,
-                   s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part);
+                   s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part,
+                   nullptr, nullptr);
         if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         KernelTimer kt("gemm.splitk_reduce", s);
         const int64_t n = M * ((N + 3) / 4);
@@ -694,17 +681,18 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
 // bf16 rows of twice the length (K, lda, ldb doubled); only the MFMAs read them as floats
 template <int ROLE, int BM, int BN, int NS, int WM, int WN, bool MB16 = false>
 hipError_t run_dma_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B, int64_t ldb,
-                       float* C, int64_t ldc, hipStream_t s, int splits = 1, float* part = nullptr) {
+                       float* C, int64_t ldc, hipStream_t s, const SplitOperands& marks, int splits = 1,
+                       float* part = nullptr) {
     const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
     if (splits <= 1) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, 64, NS, WM, WN, true, false, true, MB16>), dim3(tm * tn), dim3(64 * WM * WN),
                    0, s, (int)M, (int)N, (int)(2 * K), (const bf16*)A, 2 * lda, (const bf16*)B, 2 * ldb, C, ldc, tm,
-                   tn, nullptr);
+                   tn, nullptr, marks.ea, marks.eb);
         return hipGetLastError();
     }
     SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, 64, NS, WM, WN, true, true, true, MB16>), dim3(tm * tn, splits),
                dim3(64 * WM * WN), 0, s, (int)M, (int)N, (int)(2 * K / splits), (const bf16*)A, 2 * lda,
-               (const bf16*)B, 2 * ldb, C, ldc, tm, tn, part);
+               (const bf16*)B, 2 * ldb, C, ldc, tm, tn, part, nullptr, nullptr);
     if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     KernelTimer kt("gemm.splitk_reduce", s);
     const int64_t n4 = M * ((N + 3) / 4);
@@ -806,6 +794,17 @@ F32Tiles f32_tiles(int64_t M, int64_t N) {
     if (c224 < c) { c = c224; best = kF32Tiles256x224; }
     if (c128x224 < c) { c = c128x224; best = kF32Tiles128x224; }
     return best;
+}
+
+// time of the float32 tiles: the same model in us (614 GFLOP/s of float32 MFMA per CU), 64x64
+// tiles at half of it
+float f32_us(F32Tiles t, int64_t M, int64_t N, int64_t K) {
+    const int bm[] = {128, 256, 256, 128, 64}, bn[] = {128, 256, 224, 224, 64};
+    const double eff[] = {0.89, 0.91, 0.93, 0.91, 0.50};
+    const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
+    const int per_cu = t == kF32Tiles128 || t == kF32Tiles64 ? 2 : 1;
+    const double rounds = t == kF32Tiles64 ? (double)tiles / (256.0 * per_cu) : (double)((tiles + 256 * per_cu - 1) / (256 * per_cu));
+    return 5.0f + (float)(rounds * per_cu * bm[t] * bn[t] * 2.0 * K / (eff[t] * 614.4e3));
 }
 
 // Decode batches above the few-row kernels (65..512 rows) with bf16 output: the streamed
@@ -1105,7 +1104,8 @@ size_t f32_splitk_bytes(int64_t M, int64_t N, int64_t K) {
 }  // namespace
 
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role) {
-    if (a_dt == SSM_F32 && b_dt == SSM_F32) return f32_splitk_bytes(M, N, K);
+    // K-slices or halves, one or the other
+    if (a_dt == SSM_F32 && b_dt == SSM_F32) return std::max(f32_splitk_bytes(M, N, K), gemm_f32_halves_bytes(M, N, K));
     if (M <= 64 || N == 0 || b_dt != SSM_BF16 || a_dt != SSM_BF16 || K % 64 != 0) return 0;
     if (role == kGemmXProj && M <= 512 && N <= 256) return 0;  // few-row kernel or whole tiles
     // the most that a choice of pick_tile's can use
@@ -1149,7 +1149,7 @@ size_t gemm_decode_scratch(int64_t M, int64_t N, int64_t K, int dt, GemmRole rol
 
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt, const void* B,
                           int64_t ldb, int b_dt, void* C, int64_t ldc, int c_dt, hipStream_t s, GemmRole role,
-                          float* scratch, size_t scratch_bytes) {
+                          float* scratch, size_t scratch_bytes, void* halves, size_t halves_bytes) {
     if (M == 0 || N == 0) return hipSuccess;
     if (b_dt == SSM_F32) {
         // up to 64 rows (a decode step): the weight stream in whole lines
@@ -1185,28 +1185,52 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
             const int64_t tm2 = (M + 127) / 128, tn2 = (N + 127) / 128;
             const bool few = f32_slices(tm2 * tn2, K) > 1;
             const int sp = few ? fit_slices(f32_slices(((M + 63) / 64) * ((N + 63) / 64), K), M, N, scratch_bytes) : 1;
-            if (K % kF32BK == 0 && (tm2 * tn2 >= 256 || few) && lda % 4 == 0 && ldb % 4 == 0 && al16(A) &&
-                al16(B) && al16(C) && 256 * lda * 4 < ((int64_t)1 << 31) && 256 * ldb * 4 < ((int64_t)1 << 31)) {
-                const F32Tiles t = few ? kF32Tiles64 : f32_tiles(M, N);
+            if (K % kF32BK == 0 && lda % 4 == 0 && ldb % 4 == 0 && al16(A) && al16(B) && al16(C) &&
+                256 * lda * 4 < ((int64_t)1 << 31) && 256 * ldb * 4 < ((int64_t)1 << 31)) {
+                const bool many = tm2 * tn2 >= 256;
+                const F32Tiles t = many && !few ? f32_tiles(M, N) : kF32Tiles64;
                 float* part = sp > 1 ? scratch : nullptr;
                 const float* fA = (const float*)A;
                 const float* fB = (const float*)B;
                 float* fC = (float*)C;
+                // as f16 halves on the f16 cores when that is faster and no less exact: its
+                // distance from float64 is 1.13e-8 sqrt(K) (2-norm, measured over the shapes of
+                // gemm_split.hip), that of these tiles 1.79e-8 sqrt(K / slices), so it is the
+                // smaller up to two slices. The tiles then run behind it for the rows and
+                // columns it left out.
+                SplitOperands marks{};
+                const size_t hb = gemm_f32_halves_bytes(M, N, K);
+                if (hb > 0 && hb <= halves_bytes && sp <= 2 && gemm_f32_split_us(M, N, K) < f32_us(t, M, N, K)) {
+                    const hipError_t e = launch_gemm_f32_split(role, M, N, K, fA, lda, fB, ldb, fC, ldc, halves, s, &marks);
+                    if (e != hipSuccess) return e;
+                    part = nullptr;
+                }
+                const int slices = marks.ea ? 1 : sp;
 #define SSM_F32_DMA(R)                                                                                         \
     case R:                                                                                                    \
         switch (t) {                                                                                           \
-            case kF32Tiles256: return run_dma_f32<R, 256, 256, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
-            case kF32Tiles256x224: return run_dma_f32<R, 256, 224, 2, 8, 1>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
-            case kF32Tiles128x224: return run_dma_f32<R, 128, 224, 2, 4, 2, true>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
-            case kF32Tiles64: return run_dma_f32<R, 64, 64, 4, 2, 2>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, sp, part); \
-            default: return run_dma_f32<R, 128, 128, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
+            case kF32Tiles256: return run_dma_f32<R, 256, 256, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
+            case kF32Tiles256x224: return run_dma_f32<R, 256, 224, 2, 8, 1>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
+            case kF32Tiles128x224: return run_dma_f32<R, 128, 224, 2, 4, 2, true>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
+            case kF32Tiles64: return run_dma_f32<R, 64, 64, 4, 2, 2>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks, slices, part); \
+            default: return run_dma_f32<R, 128, 128, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
         }
-                switch (role) {
-                    SSM_F32_DMA(kGemmInProj)
-                    SSM_F32_DMA(kGemmXProj)
-                    SSM_F32_DMA(kGemmDtProj)
-                    SSM_F32_DMA(kGemmOutProj)
-                    default: SSM_F32_DMA(kGemmGeneric)
+                auto tiles = [&]() -> hipError_t {
+                    switch (role) {
+                        SSM_F32_DMA(kGemmInProj)
+                        SSM_F32_DMA(kGemmXProj)
+                        SSM_F32_DMA(kGemmDtProj)
+                        SSM_F32_DMA(kGemmOutProj)
+                        default: SSM_F32_DMA(kGemmGeneric)
+                    }
+                    return hipErrorInvalidValue;
+                };
+                if (!marks.ea) {
+                    // (few tiles and a K that does not slice: the register-staged tiles below)
+                    if (many || few) return tiles();
+                } else {
+                    KernelTimer kt("gemm.f32_marked", s);
+                    return tiles();
                 }
 #undef SSM_F32_DMA
             }

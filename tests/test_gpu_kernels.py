@@ -183,6 +183,76 @@ def test_gemm_bf16_tiles(B, role, M, N, K):
                      f"{role} {M}x{N}x{K} scratch {0 if sc is None else need}")
 
 
+# one shape per tile of the float32 products on f16 halves (64x64, 64x128, 96x128, 128x128, 192x128,
+# 256x128, 192x256, 256x256), ragged in M and N, odd and even numbers of 32-wide stages
+F32_HALVES_SHAPES = [(129, 5123, 320), (391, 2601, 320), (517, 3587, 352), (1499, 2051, 320), (1029, 3589, 96),
+                     (3999, 1543, 128), (2599, 3077, 96), (3999, 3077, 96), (700, 2600, 2560)]
+
+
+def _f32_pair(B, A, Bm, M, N, K):
+    """The product with the scratch its halves need, and on float32 operands without scratch."""
+    Np = (N + 3) // 4 * 4
+    out = []
+    need = B.gemm_splitk_bytes(M, N, K, B.SSM_F32, B.SSM_F32, "in_proj")
+    for scratch in (torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda"), None):
+        C = torch.full((M, Np), float("nan"), dtype=torch.float32, device="cuda")[:, :N]
+        B.ssm_gemm_nt_role(A, Bm, C, "in_proj", scratch)
+        torch.cuda.synchronize()
+        out.append(C.to(torch.float64).cpu().numpy())
+    return out
+
+
+@pytest.mark.parametrize("M,N,K", F32_HALVES_SHAPES)
+def test_gemm_f32_halves(B, M, N, K):
+    """Float32 products of prefill size on f16 halves: no further from the float64 product than
+    the float32 tiles, with rows and columns of very different scales (each is scaled on its
+    own) and zero rows. Bound: each product is off by at most 2^-24 (the left-out lo x lo) +
+    2 x 2^-24 (the operands' residuals), and about 3 K / 32 sums are rounded to float32."""
+    rng = np.random.default_rng(M + 7 * N + K)
+    A = _rnd_host(rng, (M, K), "f32") * np.float32(10.0) ** rng.integers(-30, 30, (M, 1)).astype(np.float32)
+    Bm = _rnd_host(rng, (N, K), "f32", 1.0 / np.sqrt(K)) * np.float32(10.0) ** rng.integers(-6, 6, (N, 1)).astype(np.float32)
+    A[M // 2] = 0.0
+    Bm[N // 3] = 0.0
+    halves, tiles = _f32_pair(B, _dev(A, torch.float32), _dev(Bm, torch.float32), M, N, K)
+    ref = A.astype(np.float64) @ Bm.astype(np.float64).T
+    assert (halves != tiles).any(), "the halves path is expected to run"
+    # each output against the norms of its row and column
+    scale = np.linalg.norm(A.astype(np.float64), axis=1)[:, None] * np.linalg.norm(Bm.astype(np.float64), axis=1)[None]
+    scale[scale == 0.0] = 1.0
+    eh, et = np.abs(halves - ref) / scale, np.abs(tiles - ref) / scale
+    bound = 2.0 ** -24 * (3.0 + np.sqrt(3.0 * K / 32.0))   # random roundings add up as their root
+    assert eh.max() <= 2.0 * bound, f"largest error {eh.max():.3e}, bound {bound:.3e}"
+    assert np.sqrt((eh ** 2).mean()) <= np.sqrt((et ** 2).mean()), "further from float64 than the float32 tiles"
+
+
+@pytest.mark.parametrize("M,N,K", [(391, 2601, 320), (3999, 1543, 128), (700, 2600, 2560)])
+def test_gemm_f32_halves_marked_rows(B, M, N, K):
+    """Rows that two f16 halves do not suit: infinities, NaN, values at the top of the range, and
+    a bulk far below the row's largest value (which meets zeros of the other operand). Their
+    outputs come from the float32 tiles, bit for bit, and the others are not touched by them."""
+    rng = np.random.default_rng(M + N)
+    A, Bm = _rnd_host(rng, (M, K), "f32"), _rnd_host(rng, (N, K), "f32", 1.0 / np.sqrt(K))
+    clean = A.astype(np.float64) @ Bm.astype(np.float64).T
+    A[3, 5], A[M - 1, K - 1] = np.inf, np.nan
+    A[M // 2] *= np.float32(2.0 ** -24)
+    A[M // 2, 0] = 1.0
+    Bm[N - 2, 1] = -np.inf
+    Bm[7] *= np.float32(2.0 ** 100)   # a large scale alone marks nothing
+    Bm[:, 0] = 0.0
+    A[:, 0] = np.where(np.arange(M) == M // 2, np.float32(1.0), np.float32(0.0))
+    halves, tiles = _f32_pair(B, _dev(A, torch.float32), _dev(Bm, torch.float32), M, N, K)
+    for r in (3, M // 2, M - 1):
+        np.testing.assert_array_equal(halves[r], tiles[r])
+    np.testing.assert_array_equal(halves[:, N - 2], tiles[:, N - 2])
+    rows = np.setdiff1d(np.arange(M), [3, M // 2, M - 1])
+    cols = np.setdiff1d(np.arange(N), [N - 2])
+    with np.errstate(invalid="ignore"):
+        ref = A.astype(np.float64) @ Bm.astype(np.float64).T
+    got, ref = halves[np.ix_(rows, cols)], ref[np.ix_(rows, cols)]
+    assert np.isfinite(got).all() and np.isfinite(clean).all()
+    assert np.abs((got - ref) / np.maximum(np.linalg.norm(ref, axis=0), 1e-30) * np.sqrt(len(rows))).max() <= 2e-5
+
+
 F32_SPLITK_SHAPES = [("x_proj", 2048, 256, 3584), ("x_proj", 2000, 256, 3584), ("in_proj", 256, 3072, 768),
                      ("out_proj", 300, 770, 1536), ("generic", 129, 130, 1024)]
 

@@ -298,8 +298,31 @@ SkinnyArgs skinny(const void* A, int64_t lda, bool a_f32, const void* B, int64_t
 
 #define SSM_SKINNY(name, s, p, epi) SSM_TIMED(name, s, launch_gemm_skinny(p, epi, s))
 
+// The residual stream around a stack's mixer, taken into its projections (up to 16 rows, bf16):
+// out_proj adds to resid and leaves the tiles' sums of squares in rss, and the next layer's
+// in_proj normalises resid by them. null: the mixer reads x and writes y.
+struct ResidualIo {
+    float *resid, *rss;
+    int nrss;
+    const float* norm_w;  // of this layer, when its in_proj reads the residual (else null: x is normed)
+    float eps;
+    bool add;             // its out_proj adds to the residual (else y is written)
+};
+
+// K-slices of the x_proj of a decode step that keeps its x_dbl to itself (no exchange): 4 from
+// 3072 channels on, up to 16 sequences (the 2.8B layer's x_proj 7.6 -> 4.0 us, the state step that
+// adds them 5.6 -> 5.9 us; at 2560 channels and fewer one slice runs at the 4 us of a launch). The
+// partials take dt's room in the workspace, which the fused state step does not use.
+int decode_xslices(const ssm_shard_desc_t* d, int32_t B) {
+    const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state;
+    const bool ok = d->act_dtype == SSM_BF16 && d->d_conv >= 2 && B <= 16 && E >= 3072 && E <= 10240 && E % 256 == 0 &&
+                    d->dt_rank <= 512 && 4 * W * 4 <= E * 2;
+    return ok ? 4 : 1;
+}
+
 int decode1(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void* x, int32_t B, const int32_t* slot,
-            void* conv_pool, int32_t S, float* xdbl, const DecodeWs& L, hipStream_t s) {
+            void* conv_pool, int32_t S, float* xdbl, const DecodeWs& L, hipStream_t s, int xs = 1,
+            const ResidualIo* io = nullptr) {
     const int adt = d->act_dtype;
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state, dm = d->d_model;
     if (adt == SSM_BF16 && d->d_conv >= 2 && B <= kConvEpilogueMax) {
@@ -309,8 +332,16 @@ int decode1(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void*
         p.conv_w = w->conv_w; p.conv_b = w->conv_b; p.conv_pool = conv_pool; p.Kc = d->d_conv;
         p.conv_lo = 0; p.conv_n = (int)E; p.u = L.u;
         SkinnyArgs q = skinny(L.u, E, false, w->x_proj_w, E, xdbl, W, B, W, E);
-        SSM_SKINNY("decode.in_proj_conv", s, p, kSkinnyConv);
-        SSM_SKINNY("decode.x_proj", s, q, kSkinnyStoreF32);
+        if (io && io->norm_w) {
+            p.A = io->resid; p.a_f32 = true;
+            p.rss = io->rss; p.nrss = io->nrss; p.nrm_w = io->norm_w; p.nrm_eps = io->eps;
+            SSM_TIMED("decode.in_proj_conv", s, launch_gemv_rms_conv(p, s));
+        } else {
+            SSM_SKINNY("decode.in_proj_conv", s, p, kSkinnyConv);
+        }
+        q.kslices = xs;
+        if (xs > 1) SSM_TIMED("decode.x_proj", s, launch_gemv_slices(q, s));
+        else SSM_SKINNY("decode.x_proj", s, q, kSkinnyStoreF32);
         return SSM_OK;
     }
     if (adt == SSM_F32 && d->d_conv >= 2) {
@@ -337,7 +368,8 @@ int decode1(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void*
 }
 
 int decode2(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const float* xdbl, int32_t B,
-            const int32_t* slot, float* ssm_pool, int32_t S, void* y, const DecodeWs& L, hipStream_t s) {
+            const int32_t* slot, float* ssm_pool, int32_t S, void* y, const DecodeWs& L, hipStream_t s, int xs = 1,
+            const ResidualIo* io = nullptr) {
     const int adt = d->act_dtype;
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state, dm = d->d_model, R = d->dt_rank;
     if (adt == SSM_BF16 && B <= kFusedDecodeMax) {
@@ -346,10 +378,15 @@ int decode2(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const float
         p.slot = slot; p.S = S; p.status = L.status; p.E = (int)E;
         p.u = L.u; p.z = L.xz + E * act_bytes(d); p.ld_z = 2 * E;
         p.xdbl = xdbl; p.ld_xdbl = W; p.R = (int)R; p.b_dt = w->dt_proj_b; p.A_log = w->A_log; p.D = w->D;
-        p.pool = ssm_pool; p.g = L.g;
+        p.pool = ssm_pool; p.g = L.g; p.xs = xs; p.xs_stride = (int64_t)B * W;
         SkinnyArgs q = skinny(L.g, E, false, w->out_proj_w, E, y, dm, B, dm, E);
         SSM_SKINNY("decode.dt_proj_state", s, p, kSkinnyState);
-        SSM_SKINNY("decode.out_proj", s, q, kSkinnyStoreBf16);
+        if (io && io->add) {
+            q.resid = io->resid; q.rss = io->rss; q.nrss = io->nrss;
+            SSM_TIMED("decode.out_proj", s, launch_gemv_resid(q, s));
+        } else {
+            SSM_SKINNY("decode.out_proj", s, q, kSkinnyStoreBf16);
+        }
         return SSM_OK;
     }
     ScanArgs sa = scan_args(d, w, L.u, L.dt, L.xz, xdbl, B, nullptr, slot, nullptr, B, ssm_pool, S, L.g, L.status,
@@ -370,6 +407,16 @@ int decode2(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const float
     SSM_TRY(gemm(B, dm, E, L.g, E, adt, w->out_proj_w, E, adt, y, dm, adt, s, "decode.out_proj", kGemmOutProj,
                  L.splitk));
     return SSM_OK;
+}
+
+// both stages with the exchange as identity: x_dbl stays inside, so x_proj may leave K-slices
+int decode_both(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void* x, int32_t B, const int32_t* slot,
+                void* conv_pool, float* ssm_pool, int32_t S, void* y, const DecodeWs& L, hipStream_t s,
+                const ResidualIo* io = nullptr) {
+    const int xs = decode_xslices(d, B);
+    float* xdbl = xs > 1 ? (float*)L.dt : L.xdbl;
+    SSM_TRY(decode1(d, w, x, B, slot, conv_pool, S, xdbl, L, s, xs, io));
+    return decode2(d, w, xdbl, B, slot, ssm_pool, S, y, L, s, xs, io);
 }
 
 int prefill_checks(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, int64_t T, const ssm_seq_meta_t* m,
@@ -570,8 +617,7 @@ int ssm_shard_decode_step(const ssm_shard_desc_t* d, const ssm_shard_weights_t* 
         SSM_TRY(check_ptr(x, "x_t"));
         SSM_TRY(check_ptr(y, "y_partial"));
     }
-    SSM_TRY(decode1(d, w, x, B, slot, conv_pool, S, L.xdbl, L, s));
-    return decode2(d, w, L.xdbl, B, slot, ssm_pool, S, y, L, s);
+    return decode_both(d, w, x, B, slot, conv_pool, ssm_pool, S, y, L, s);
 }
 
 int ssm_shard_decode_step_noalloc(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void* x,
@@ -595,8 +641,7 @@ int ssm_shard_decode_step_noalloc(const ssm_shard_desc_t* d, const ssm_shard_wei
     void* base = nullptr;
     SSM_TRY(scratch_address(s, &base));
     const DecodeWs L = decode_layout(d, B, base);
-    SSM_TRY(decode1(d, w, x, B, slot, conv_pool, S, L.xdbl, L, s));
-    return decode2(d, w, L.xdbl, B, slot, ssm_pool, S, y, L, s);
+    return decode_both(d, w, x, B, slot, conv_pool, ssm_pool, S, y, L, s);
 }
 
 int ssm_shard_slice_weights(const ssm_shard_desc_t* d, const ssm_shard_weights_t* full, const ssm_shard_weights_t* out,
@@ -1322,11 +1367,32 @@ int ssm_stack_decode_step(const ssm_stack_desc_t* sd, const ssm_shard_weights_t*
     NormParts none{};
     SSM_TIMED("layer.residual_rmsnorm", s,
               launch_residual_rmsnorm(x, bf, none, bf, B.resid, norm_w[0], eps, B.normed, bf, Bsz, dm, s));
+    // Up to 16 rows in bf16, the add and the norm between two layers run inside their projections
+    // (the norm kernel in front of the first and behind the last layer stays): per layer of the
+    // 2.8B stack at batch 1 the norm's 4.2 us go, in_proj takes 10.9 -> 13.2 and out_proj 6.6 ->
+    // 7.5 us (timed one by one); the eight layers' step, with the K-slices, 308 -> 262 us. y is not
+    // stored then, and its room holds the sums of squares.
+    ResidualIo io{};
+    io.resid = B.resid; io.rss = (float*)B.y; io.nrss = (dm + 15) / 16; io.eps = eps;
+    const int64_t E = d->d_inner_shard;
+    bool fuse = bf && d->d_conv >= 2 && Bsz <= 16 && sd->n_layers > 1;
+    if (fuse) {
+        const SkinnyArgs out = skinny(L.g, E, false, layers[0].out_proj_w, E, B.y, dm, Bsz, dm, E);
+        const SkinnyArgs in = skinny(B.resid, dm, true, layers[0].in_proj_w, dm, L.xz, 2 * E, Bsz, 2 * E, dm);
+        fuse = gemv_resid_fits(out) && gemv_rms_fits(in);
+    }
     for (int l = 0; l < sd->n_layers; ++l) {
-        SSM_TRY(decode1(d, &layers[l], B.normed, Bsz, slot, conv_pools[l], S, L.xdbl, L, s));
-        if (sd->bcdt_eps > 0.0f) SSM_TIMED("layer.bcdt_rms", s, launch_bcdt_rms(L.xdbl, Bsz, R, N, W, sd->bcdt_eps, s));
-        SSM_TRY(decode2(d, &layers[l], L.xdbl, Bsz, slot, ssm_pools[l], S, B.y, L, s));
         const bool last = l + 1 == sd->n_layers;
+        io.norm_w = fuse && l > 0 ? norm_w[l] : nullptr;
+        io.add = fuse && !last;
+        if (sd->bcdt_eps > 0.0f) {
+            SSM_TRY(decode1(d, &layers[l], B.normed, Bsz, slot, conv_pools[l], S, L.xdbl, L, s, 1, &io));
+            SSM_TIMED("layer.bcdt_rms", s, launch_bcdt_rms(L.xdbl, Bsz, R, N, W, sd->bcdt_eps, s));
+            SSM_TRY(decode2(d, &layers[l], L.xdbl, Bsz, slot, ssm_pools[l], S, B.y, L, s, 1, &io));
+        } else {
+            SSM_TRY(decode_both(d, &layers[l], B.normed, Bsz, slot, conv_pools[l], ssm_pools[l], S, B.y, L, s, &io));
+        }
+        if (io.add) continue;
         SSM_TIMED("layer.residual_rmsnorm", s,
                   launch_residual_rmsnorm(B.resid, false, one_part(B.y), bf, B.resid, last ? final_w : norm_w[l + 1],
                                           eps, last ? out : B.normed, bf, Bsz, dm, s));

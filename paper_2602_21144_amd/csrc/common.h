@@ -38,6 +38,10 @@ __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
 }
 
+__device__ __forceinline__ float buffer_load_f32(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+
 // Global -> LDS on the DMA path: buffer_load_dwordx4 ... lds writes each lane's 16 bytes
 // at lane slot (lane * 16) of a 1 KB LDS block at lds_addr (M0), with no staging
 // registers. The source is the buffer resource r at byte offset voff (per lane) + soff
@@ -205,11 +209,28 @@ struct SkinnyArgs {
     // gated RMSNorm applied to A as it is loaded (Mamba-2 out_proj): column c of row m is
     // multiplied by 1 / sqrt(sumsq[m][k] / gsize + eps) and norm_w[c], k = (c0 + c) / gsize
     const float* nrm_sumsq; const float* nrm_w; int nrm_G, nrm_gsize, nrm_c0; float nrm_eps;
+    // K-slices (streamed kernel, float32 stores): slice y of the grid sums K / kslices of the
+    // products into C + y * M * ldc; the state step adds xs slices of xdbl, xs_stride apart
+    int kslices; int xs; int64_t xs_stride;
+    // the residual stream of a stack's decode step: resid [M][ldc] float32 and, per row, the
+    // sums of squares of its 16-column tiles, rss [M][nrss]. An out_proj adds its output (rounded
+    // to bf16) to resid and writes the sums; the next in_proj reads resid as A, normalised by
+    // them with the weights nrm_w and nrm_eps
+    float* resid; float* rss; int nrss;
 };
 hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s);
 // the streamed kernel with the norm prologue above (plain bf16 stores); hipErrorNotSupported
 // when the shape does not suit it (the caller then runs the norm and the product apart)
 hipError_t launch_gemv_norm(const SkinnyArgs& p, hipStream_t s);
+// the streamed kernel on K-slices (kslices, float32 partials); hipErrorNotSupported when the
+// shape does not suit it
+hipError_t launch_gemv_slices(const SkinnyArgs& p, hipStream_t s);
+// the streamed kernel with the residual epilogue, and with the conv epilogue on an A that is
+// normalised from the residual; gemv_resid_fits and gemv_rms_fits say whether a shape suits them
+bool gemv_resid_fits(const SkinnyArgs& p);
+bool gemv_rms_fits(const SkinnyArgs& p);
+hipError_t launch_gemv_resid(const SkinnyArgs& p, hipStream_t s);
+hipError_t launch_gemv_rms_conv(const SkinnyArgs& p, hipStream_t s);
 // Few-row product with float32 operands, C[M][N] = A[M][K] * B[N][K]^T in float32 (the
 // decode projections of a float32 layer); role (GemmRole) only names the kernel instance.
 // hipErrorNotSupported when the shape does not suit it (M > 64, K % 32, unaligned rows).

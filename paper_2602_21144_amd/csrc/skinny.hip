@@ -18,13 +18,15 @@
 //             (window shifted in place), the other columns (gate, Mamba-2's dt) are stored;
 //   kEpiState (dt_proj): Delta = softplus(dt + b_dt), one recurrence step on the cached
 //             state in place, D skip and SiLU gate -> g;
-//   kEpiStore: plain store (x_proj in fp32, out_proj in bf16).
+//   kEpiStore: plain store (x_proj in fp32, out_proj in bf16);
+//   kEpiResid (out_proj inside a stack): the output is added to the float32 residual stream, and
+//             each tile leaves its rows' sums of squares for the norm in front of the next mixer.
 #include "common.h"
 
 namespace ssm {
 namespace {
 
-enum Epi { kEpiStoreBf16 = 0, kEpiStoreF32 = 1, kEpiConv = 2, kEpiState = 3 };
+enum Epi { kEpiStoreBf16 = 0, kEpiStoreF32 = 1, kEpiConv = 2, kEpiState = 3, kEpiResid = 4 };
 
 // An A fragment as loaded: 8 bf16, or 8 fp32 rounded to bf16 when it enters the MFMA.
 template <bool A_F32> struct ARaw {
@@ -37,6 +39,10 @@ template <> struct ARaw<true> {
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
         v0 = buffer_load16(r, off);
         v1 = buffer_load16(r, off == kOffOutOfRange ? off : off + 16);
+    }
+    __device__ __forceinline__ void add(const ARaw& o) {
+        v0 = __builtin_bit_cast(u32x4, __builtin_bit_cast(f32x4, v0) + __builtin_bit_cast(f32x4, o.v0));
+        v1 = __builtin_bit_cast(u32x4, __builtin_bit_cast(f32x4, v1) + __builtin_bit_cast(f32x4, o.v1));
     }
     __device__ __forceinline__ bf16x8 get() const {
         const f32x4 x = __builtin_bit_cast(f32x4, v0), y = __builtin_bit_cast(f32x4, v1);
@@ -121,7 +127,8 @@ template <> struct EpiIn<kEpiState> {
     int slot;
     float h[kN], a[kN], bc[2 * kN], u, z, bdt, Dn;
     __device__ __forceinline__ void load_slot(const SkinnyArgs& p, int m) { slot = p.slot[m]; }
-    __device__ __forceinline__ void load(const SkinnyArgs& p, int m, int n) {
+    // NSL > 1: xdbl is in K-slices, whose B and C the kernel adds itself (once per row)
+    template <int NSL> __device__ __forceinline__ void load(const SkinnyArgs& p, int m, int n) {
         const int sc = slot_ok(slot, p.S) ? slot : 0;
         const float4* hp = (const float4*)(p.pool + ((int64_t)sc * p.E + n) * kN);
         const float4* al = (const float4*)(p.A_log + (int64_t)n * kN);
@@ -132,10 +139,12 @@ template <> struct EpiIn<kEpiState> {
             h[4 * q] = hv.x; h[4 * q + 1] = hv.y; h[4 * q + 2] = hv.z; h[4 * q + 3] = hv.w;
             a[4 * q] = av.x; a[4 * q + 1] = av.y; a[4 * q + 2] = av.z; a[4 * q + 3] = av.w;
         }
+        if constexpr (NSL == 1) {
 #pragma unroll
-        for (int q = 0; q < 2 * kN / 4; ++q) {
-            const float4 bv = bt[q];
-            bc[4 * q] = bv.x; bc[4 * q + 1] = bv.y; bc[4 * q + 2] = bv.z; bc[4 * q + 3] = bv.w;
+            for (int q = 0; q < 2 * kN / 4; ++q) {
+                const float4 bv = bt[q];
+                bc[4 * q] = bv.x; bc[4 * q + 1] = bv.y; bc[4 * q + 2] = bv.z; bc[4 * q + 3] = bv.w;
+            }
         }
         u = (float)((const bf16*)p.u)[(int64_t)m * p.E + n];
         z = (float)((const bf16*)p.z)[(int64_t)m * p.ld_z + n];
@@ -165,13 +174,22 @@ template <> struct EpiIn<kEpiState> {
     }
 };
 
+// out_proj inside a stack: the residual element that the output is added to
+template <> struct EpiIn<kEpiResid> {
+    float r;
+    __device__ __forceinline__ void load_slot(const SkinnyArgs&, int) {}
+    __device__ __forceinline__ void load(const SkinnyArgs& p, int m, int n) { r = p.resid[(int64_t)m * p.ldc + n]; }
+};
+
 // NW waves split K; every thread owns at most one output element of the 16-column tile
 // (NW * 64 >= MB * 16). Each wave issues the loads of up to KU k-steps (32 each) before
 // its MFMAs; the first batch goes out right after the epilogue's slot index and before
 // the epilogue operands.
-template <int MB, int NW, int KU, bool A_F32, int EPI>
+// NSL (state epilogue): A is the sum of that many K-slices of x_dbl, xs_stride floats apart.
+template <int MB, int NW, int KU, bool A_F32, int EPI, int NSL = 1>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs p) {
     static_assert(NW * 64 >= MB * 16, "one epilogue element per thread");
+    static_assert(NSL == 1 || (A_F32 && EPI == kEpiState), "slices of x_dbl");
     constexpr int MT = MB / 16;
     __shared__ float red[NW][MB * 16];
     const int n0 = blockIdx.x * 16, m0 = blockIdx.y * MB;
@@ -183,6 +201,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs p) {
     const int emc = em < p.M ? em : p.M - 1, enc = en < p.N ? en : p.N - 1;  // in-range for the fetch
     EpiIn<EPI> ein;
     ein.load_slot(p, emc);
+    // K-slices of B and C: one element of the 16 rows per thread, added in slice order
+    constexpr int kBC = 2 * kN;
+    static_assert(NSL == 1 || NW * 64 == MB * kBC, "one element of B and C per thread");
+    __shared__ __attribute__((aligned(16))) float bcs[NSL > 1 ? MB * kBC : 4];
+    float bce[NSL];
+    if constexpr (NSL > 1) {
+        const float* bp = p.xdbl + (int64_t)min(m0 + e / kBC, p.M - 1) * p.ld_xdbl + p.R + e % kBC;
+#pragma unroll
+        for (int y = 0; y < NSL; ++y) bce[y] = bp[y * p.xs_stride];
+    }
 
     const int ksteps = (p.K + 31) / 32;
     const int per = (ksteps + NW - 1) / NW;
@@ -193,13 +221,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs p) {
     constexpr int asz = A_F32 ? 4 : 2;
     const __amdgpu_buffer_rsrc_t rb =
         buffer_rsrc(p.B + (int64_t)n0 * p.ldb, (uint32_t)(min(16, p.N - n0) * p.ldb * 2));
-    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc((const char*)p.A + (int64_t)m0 * p.lda * asz,
-                                                  (uint32_t)(min(MB, p.M - m0) * p.lda * asz));
+    __amdgpu_buffer_rsrc_t ra[NSL];
+#pragma unroll
+    for (int y = 0; y < NSL; ++y)
+        ra[y] = buffer_rsrc((const char*)p.A + ((int64_t)m0 * p.lda + (NSL > 1 ? y * p.xs_stride : 0)) * asz,
+                            (uint32_t)(min(MB, p.M - m0) * p.lda * asz));
     f32x4 acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i] = f32x4{};
     u32x4 bf[KU];
-    ARaw<A_F32> af[KU][MT];
+    ARaw<A_F32> af[KU][MT][NSL];
     auto load_batch = [&](int s) {
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
@@ -208,22 +239,30 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs p) {
             bf[u] = buffer_load16(rb, kok ? (uint32_t)(((lane & 15) * p.ldb + k) * 2) : kOffOutOfRange);
 #pragma unroll
             for (int i = 0; i < MT; ++i)
-                af[u][i].load(ra, kok ? (uint32_t)(((i * 16 + (lane & 15)) * p.lda + k) * asz) : kOffOutOfRange);
+#pragma unroll
+                for (int y = 0; y < NSL; ++y)
+                    af[u][i][y].load(ra[y], kok ? (uint32_t)(((i * 16 + (lane & 15)) * p.lda + k) * asz) : kOffOutOfRange);
         }
     };
     auto mma_batch = [&]() {
 #pragma unroll
         for (int u = 0; u < KU; ++u)
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][i].get(), __builtin_bit_cast(bf16x8, bf[u]),
+            for (int i = 0; i < MT; ++i) {
+                if constexpr (NSL > 1) {
+#pragma unroll
+                    for (int y = 1; y < NSL; ++y) af[u][i][0].add(af[u][i][y]);
+                }
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][i][0].get(), __builtin_bit_cast(bf16x8, bf[u]),
                                                                  acc[i], 0, 0, 0);
+            }
     };
     load_batch(s0);
     // keep the order: weights in flight, then the slot-addressed epilogue fetch (which waits
     // only for the slot index), then the MFMAs (which wait for the weights)
     __builtin_amdgcn_sched_barrier(0);
-    ein.load(p, emc, enc);
+    if constexpr (EPI == kEpiState) ein.template load<NSL>(p, emc, enc);
+    else ein.load(p, emc, enc);
     __builtin_amdgcn_sched_barrier(0);
     mma_batch();
     for (int s = s0 + KU; s < s1; s += KU) {
@@ -235,8 +274,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs p) {
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[wave][(i * 16 + 4 * (lane >> 4) + r) * 16 + (lane & 15)] = acc[i][r];
+    if constexpr (NSL > 1) {
+        float b = bce[0];
+#pragma unroll
+        for (int y = 1; y < NSL; ++y) b += bce[y];
+        bcs[e] = b;
+    }
     __syncthreads();
     if (!ework) return;
+    if constexpr (NSL > 1) {
+#pragma unroll
+        for (int j = 0; j < kBC; ++j) ein.bc[j] = bcs[e / 16 * kBC + j];
+    }
     float v = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) v += red[w][e];
@@ -361,15 +410,25 @@ __device__ __forceinline__ int gemv_swz(int row, int chunk) { return chunk ^ ((r
 
 constexpr int kNormMaxK = 8192, kNormMaxMG = 256;  // norm prologue: K columns, rows x groups
 
-template <int NW, int NST, int XB, int EPI, bool NORM = false>
+// RMS (in_proj inside a stack): A is the float32 residual, scaled by each row's inverse RMS (its
+// tiles' sums of squares) and by nrm_w, rounded to bf16: the norm kernel's
+// arithmetic on the operand, while the weights are in flight. KSL: slice blockIdx.y of K (p.K is
+// one slice's) into its own C.
+template <int NW, int NST, int XB, int EPI, bool NORM = false, bool RMS = false, bool KSL = false>
 __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
+    static_assert(!(NORM && RMS) && (!KSL || EPI == kEpiStoreF32), "one norm; float32 slices");
+    if constexpr (KSL) {
+        p.A = (const bf16*)p.A + (int64_t)blockIdx.y * p.K;
+        p.B += (int64_t)blockIdx.y * p.K;
+        p.C = (float*)p.C + (int64_t)blockIdx.y * p.M * p.ldc;
+    }
     static_assert(NW >= 4, "one epilogue element per thread of the first 256");
     constexpr int SLOT = (2 + XB) * 1024;  // one stage: 16 weight rows, then 8 * XB activation rows, 128 B each
     __shared__ __attribute__((aligned(16))) char tr[NW][2][SLOT];
     __shared__ float red[NW][256];
     // norm prologue: norm_w over K and the per-(row, group) inverse RMS, staged once
-    __shared__ __attribute__((aligned(16))) float nrm_w[NORM ? kNormMaxK : 4];
-    __shared__ float nrm_inv[NORM ? kNormMaxMG : 1];
+    __shared__ __attribute__((aligned(16))) float nrm_w[NORM ? kNormMaxK : RMS ? NW * NST * kGemvBK : 4];
+    __shared__ float nrm_inv[NORM ? kNormMaxMG : RMS ? 16 : 1];
     const int n0 = blockIdx.x * 16;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
@@ -387,7 +446,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
     // activation rows past M lie outside the resources and read as zero
     const int lr = lane >> 3, lp = lane & 7;
     const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(p.B + (int64_t)n0 * p.ldb, (uint32_t)(min(16, p.N - n0) * p.ldb * 2));
-    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(p.A, (uint32_t)(p.M * p.lda * 2));
+    constexpr int ASZ = RMS ? 4 : 2, AV = RMS ? 2 : 1;  // bytes of an activation, 16-byte pieces of 8
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(p.A, (uint32_t)(p.M * p.lda * ASZ));
     const uint32_t k0b = (uint32_t)(sb * kGemvBK + lp * 8) * 2;
     const uint32_t wo0 = (uint32_t)(lr * p.ldb) * 2 + k0b, wo1 = (uint32_t)((8 + lr) * p.ldb) * 2 + k0b;
     // norm prologue operands go out first, so that waiting for them waits for nothing else
@@ -403,7 +463,23 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
         if ((int)threadIdx.x < p.M * p.nrm_G) ssq = p.nrm_sumsq[threadIdx.x];
         __builtin_amdgcn_sched_barrier(0);
     }
-    u32x4 w0[NST], w1[NST], xv[NST][XB];
+    // (RMS) this thread's share of one row's sums of squares (at most NST tiles, since K is at
+    // most NW * NST stages) and of this wave's norm weights
+    constexpr int LPR = NW * 64 / 16;  // lanes per row
+    float rs[RMS ? NST : 1], rw[RMS ? NST : 1];
+    if constexpr (RMS) {
+        const int m = threadIdx.x / LPR;
+        const __amdgpu_buffer_rsrc_t rr = buffer_rsrc(p.rss, (uint32_t)(p.M * p.nrss * 4));
+        const __amdgpu_buffer_rsrc_t rn = buffer_rsrc(p.nrm_w, (uint32_t)(p.K * 4));
+#pragma unroll
+        for (int st = 0; st < NST; ++st) {
+            const int i = threadIdx.x % LPR + st * LPR;
+            rs[st] = buffer_load_f32(rr, i < p.nrss ? (uint32_t)(m * p.nrss + i) * 4 : kOffOutOfRange);
+            rw[st] = buffer_load_f32(rn, st < nst ? (uint32_t)((sb + st) * kGemvBK + lane) * 4 : kOffOutOfRange);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    u32x4 w0[NST], w1[NST], xv[NST][XB][AV];
 #pragma unroll
     for (int st = 0; st < NST; ++st) {
         const bool ok = st < nst;
@@ -411,7 +487,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
         w1[st] = buffer_load16(rb, ok ? wo1 + st * 128 : kOffOutOfRange);
 #pragma unroll
         for (int q = 0; q < XB; ++q)
-            xv[st][q] = buffer_load16(ra, ok ? (uint32_t)((8 * q + lr) * p.lda) * 2 + k0b + st * 128 : kOffOutOfRange);
+#pragma unroll
+            for (int h = 0; h < AV; ++h)
+                xv[st][q][h] = buffer_load16(ra, ok ? (uint32_t)((8 * q + lr) * p.lda) * ASZ + (k0b + st * 128) * AV + 16 * h
+                                                    : kOffOutOfRange);
     }
     // the epilogue's slot-addressed operands go out behind the stream
     __builtin_amdgcn_sched_barrier(0);
@@ -426,6 +505,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
             if (i < p.K / 4) *(float4*)&nrm_w[4 * i] = nwr[j];
         }
         if ((int)threadIdx.x < p.M * p.nrm_G) nrm_inv[threadIdx.x] = 1.0f / sqrtf(ssq / (float)p.nrm_gsize + p.nrm_eps);
+        __syncthreads();
+    }
+    if constexpr (RMS) {
+        float q = 0.0f;
+#pragma unroll
+        for (int st = 0; st < NST; ++st) {
+            q += rs[st];
+            nrm_w[(wave * NST + st) * kGemvBK + lane] = rw[st];
+        }
+#pragma unroll
+        for (int off = LPR / 2; off >= 1; off >>= 1) q += __shfl_xor(q, off, 64);
+        if (threadIdx.x % LPR == 0) nrm_inv[threadIdx.x / LPR] = 1.0f / sqrtf(q / (float)p.K + p.nrm_eps);
         __syncthreads();
     }
     // the inverse RMS of this lane's activation rows (rows past M: 0) for one group per row
@@ -445,7 +536,19 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
             *(u32x4*)(t + (8 + lr) * 128 + gemv_swz(8 + lr, lp) * 16) = w1[st];
 #pragma unroll
             for (int q = 0; q < XB; ++q) {
-                u32x4 xq = xv[st][q];
+                u32x4 xq = xv[st][q][0];
+                if constexpr (RMS) {
+                    const float inv = nrm_inv[8 * q + lr];
+                    const f32x4 x0 = __builtin_bit_cast(f32x4, xv[st][q][0]), x1 = __builtin_bit_cast(f32x4, xv[st][q][AV - 1]);
+                    const float xs8[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+                    const float* wv = &nrm_w[(wave * NST + st) * kGemvBK + lp * 8];
+                    const f32x4 y0 = *(const f32x4*)wv, y1 = *(const f32x4*)(wv + 4);
+                    const float ws8[8] = {y0[0], y0[1], y0[2], y0[3], y1[0], y1[1], y1[2], y1[3]};
+                    bf16x8 o;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) o[i] = (bf16)(xs8[i] * inv * ws8[i]);
+                    xq = __builtin_bit_cast(u32x4, o);
+                }
                 if constexpr (NORM) {
                     const int k = (sb + st) * kGemvBK + lp * 8;
                     // one group per row (the usual case) needs no group index
@@ -473,13 +576,29 @@ __global__ __launch_bounds__(NW * 64) void gemm_gemv_kernel(SkinnyArgs p) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][(4 * (lane >> 4) + r) * 16 + (lane & 15)] = acc[r];
     __syncthreads();
+    if constexpr (EPI == kEpiResid) {
+        if (e >= 256) return;  // whole waves
+        float r = 0.0f;
+        if (ework) {
+            float v = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) v += red[w][e];
+            r = ein.r + (float)(bf16)v;
+            p.resid[(int64_t)em * p.ldc + en] = r;
+        }
+        float q = r * r;  // over the tile's columns: the 16 lanes of a row
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) q += __shfl_xor(q, off, 64);
+        if (ework && (e & 15) == 0) p.rss[em * p.nrss + blockIdx.x] = q;
+        return;
+    }
     if (!ework) return;
     float v = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) v += red[w][e];
     if constexpr (EPI == kEpiStoreBf16) ((bf16*)p.C)[(int64_t)em * p.ldc + en] = (bf16)v;
     else if constexpr (EPI == kEpiStoreF32) ((float*)p.C)[(int64_t)em * p.ldc + en] = v;
-    else ein.apply(p, em, en, v);
+    else if constexpr (EPI != kEpiResid) ein.apply(p, em, en, v);
 }
 
 // waves per workgroup for the streamed variant (0: it does not apply). Grids that fill
@@ -1080,8 +1199,64 @@ hipError_t launch_gemv_norm(const SkinnyArgs& p, hipStream_t s) {
     return hipGetLastError();
 }
 
+// x_proj of a few rows over few columns has a handful of workgroups, each streaming 16 weight
+// rows of the whole K: the 12 of the 2.8B layer (192 columns, K = 5120) took 7.6 us for 2 MB.
+// Four K-slices over four times the workgroups take 4.0 us; the state step adds the partials.
+hipError_t launch_gemv_slices(const SkinnyArgs& p, hipStream_t s) {
+    if (p.M <= 0 || p.N <= 0) return hipSuccess;
+    if (p.kslices < 2 || p.K % (p.kslices * kGemvBK) != 0 || p.K / p.kslices > 8 * 5 * kGemvBK) return hipErrorNotSupported;
+    SkinnyArgs q = p;
+    q.K /= p.kslices;
+    if (gemv_waves(q) == 0) return hipErrorNotSupported;
+    const dim3 grid((unsigned)((p.N + 15) / 16), (unsigned)p.kslices), block(8 * 64);
+    if (p.M <= 8) SSM_LAUNCH((gemm_gemv_kernel<8, 5, 1, kEpiStoreF32, false, false, true>), grid, block, 0, s, q);
+    else SSM_LAUNCH((gemm_gemv_kernel<8, 5, 2, kEpiStoreF32, false, false, true>), grid, block, 0, s, q);
+    return hipGetLastError();
+}
+
+bool gemv_resid_fits(const SkinnyArgs& p) { return gemv_waves(p) != 0; }
+// (the residual is float32: twice the activation registers, so up to 5 stages per wave, or 10
+// with at most 8 rows)
+bool gemv_rms_fits(const SkinnyArgs& p) {
+    SkinnyArgs q = p;
+    q.a_f32 = false;
+    const int nw = gemv_waves(q);
+    return (nw == 4 || (nw == 8 && (p.K / kGemvBK <= 8 * 5 || p.M <= 8))) && p.lda % 4 == 0 &&
+           (int64_t)p.M * p.lda * 4 < (int64_t)1 << 31;
+}
+
+hipError_t launch_gemv_resid(const SkinnyArgs& p, hipStream_t s) {
+    if (p.M <= 0 || p.N <= 0) return hipSuccess;
+    if (!gemv_resid_fits(p)) return hipErrorNotSupported;
+    return launch_gemv<kEpiResid>(p, gemv_waves(p), s);
+}
+
+hipError_t launch_gemv_rms_conv(const SkinnyArgs& p, hipStream_t s) {
+    if (p.M <= 0 || p.N <= 0) return hipSuccess;
+    if (!gemv_rms_fits(p)) return hipErrorNotSupported;
+    SkinnyArgs q = p;
+    q.a_f32 = false;
+    const int nw = gemv_waves(q);
+    const dim3 grid((unsigned)((p.N + 15) / 16)), block(nw * 64);
+#define SSM_GEMV_R(NW, NST, XB) SSM_LAUNCH((gemm_gemv_kernel<NW, NST, XB, kEpiConv, false, true>), grid, block, 0, s, p)
+    if (nw == 4) { if (p.M <= 8) SSM_GEMV_R(4, 5, 1); else SSM_GEMV_R(4, 5, 2); }
+    else if (p.K / kGemvBK <= 8 * 5) { if (p.M <= 8) SSM_GEMV_R(8, 5, 1); else SSM_GEMV_R(8, 5, 2); }
+    else SSM_GEMV_R(8, 10, 1);
+#undef SSM_GEMV_R
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s) {
     if (p.M <= 0 || p.N <= 0) return hipSuccess;
+    if (epi == kSkinnyState && p.xs > 1) {
+        // K-slices of x_dbl (at most 16 rows, four slices); one batch of loads per wave: with room
+        // for two at dt_rank 160 the step took 7.5 us, with one 5.9
+        if (p.M > 16 || p.xs != 4 || p.K > 8 * 2 * 32) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)((p.N + 15) / 16));
+        if (p.K <= 8 * 32) SSM_LAUNCH((gemm_skinny_kernel<16, 8, 1, true, kEpiState, 4>), grid, dim3(512), 0, s, p);
+        else SSM_LAUNCH((gemm_skinny_kernel<16, 8, 2, true, kEpiState, 4>), grid, dim3(512), 0, s, p);
+        return hipGetLastError();
+    }
     if (epi == kSkinnyStoreBf16 || epi == kSkinnyConv) {
         const hipError_t e = epi == kSkinnyConv ? launch_dtile_pick<kEpiConv>(p, s) : launch_dtile_pick<kEpiStoreBf16>(p, s);
         if (e != hipErrorNotSupported) return e;

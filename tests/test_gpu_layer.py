@@ -293,6 +293,31 @@ def test_full_width_stack_calls(act, bcdt, K):
     assert_close(host(out2), ref2["out"], TOL[act], "continued prefill")
 
 
+# batches around the 8- and 16-row tiles; widths whose projections take 4, 8 and 16 waves, one or
+# four K-slices of x_proj (3072), and more than 40 stages of K in in_proj (4096, up to 8 rows)
+@pytest.mark.parametrize("dm,E,R", [(768, 1536, 48), (2048, 3072, 64), (4096, 1024, 16)])
+@pytest.mark.parametrize("bcdt", [False, True])
+def test_stack_decode_few_rows(dm, E, R, bcdt):
+    from paper_2602_21144_amd import binding as B
+    shape = synth.LayerShape(dm, E, 16, R, 4, 1, "bf16")
+    st = synth.make_stack(shape, 3, 60, stress=True)
+    S = 17
+    layers = _oracle_stack(shape, st)
+    eps = ol.BCDT_EPS if bcdt else None
+    for Bsz in (1, 8, 9, 16, 17):
+        g = GpuStack(shape, st, bcdt, S)
+        oc, osp = _oracle_pools(shape, 3, S)
+        rng = np.random.default_rng(61 + Bsz)
+        slots = rng.permutation(S)[:Bsz].astype(np.int32)
+        for step in range(2):
+            xt = synth.make_tokens(rng, Bsz, dm, "bf16")
+            o = g.decode(_dev(xt, g.tdt), torch.from_numpy(slots).cuda())
+            d = ol.stack_decode_step(layers, st["norm_w"], st["final_w"], xt.astype(np.float64), slots, oc, osp, "bf16",
+                                     bcdt_eps=eps)
+            oc, osp = d["conv_pools"], d["ssm_pools"]
+            assert_close(host(o), d["out"], TOL["bf16"], f"stack decode of {Bsz}, step {step}")
+
+
 def test_decoding_with_and_without_the_cache():
     """The ablation's two ways of generating: prefill + decode steps from the cache, or a
     prefill of the whole prefix for every token. Both match the oracle and each other."""

@@ -476,8 +476,14 @@ __global__ __launch_bounds__(256) void decode_ssm_kernel(ScanArgs a) {
 constexpr int kDtCh = 16, kDtSeq = 4;  // tiles of the fp32 / general state-step kernel
 constexpr int kDtSeqM = 16;            // sequences per tile of the bf16 MFMA state-step kernel
 constexpr int kDtSpw = 2;              // sequences per wave of that kernel
+// float32: the tiles once the general kernel has more workgroups (ceil(nseq / 4) E / 16) than this.
+// Below it one round of small workgroups is the shorter one, above it the re-read rows count:
+// 3584 channels, dt_rank 224: 12 sequences (672) 5.9 us there and 6.1 here, 16 (896) 7.1 and 6.4,
+// 53 18.0 and 9.9; 5120 channels, dt_rank 160: 8 (640) 5.3 and 5.7, 12 (960) 6.2 and 6.0, 256 87
+// and 42; 1280 channels: 32 (640) 4.4 and 5.1, 53 (1120) 5.9 and 5.4.
+constexpr int64_t kDtF32Tiles = 768;
 
-// bf16 and dt_rank a multiple of 32 (up to 512): a workgroup takes CT tiles of 16 channels
+// dt_rank a multiple of 32 (up to 512): a workgroup takes CT tiles of 16 channels
 // (adjacent, so they share the delta rows and B, C) of 16 sequences, SPW sequences per wave
 // (four lanes per (sequence, channel), a float4 of states each: every state load and store
 // instruction covers 1 KB contiguous). The step is bound by the state bytes in flight over the
@@ -489,8 +495,13 @@ constexpr int kDtSpw = 2;              // sequences per wave of that kernel
 // thread adds them in wave order and rounds dt to bf16 as dt_proj stores it. Each workgroup
 // fetches its 16 delta rows and its W_dt rows once. (4 x 16 tiles fetched the W_dt rows once
 // per 4 sequences, about as many L2 bytes as the states themselves: 15.5 us.)
-template <int NK, int SPW, int CT>
+//
+// float32: the chunk is eight v_mfma_f32_16x16x4_f32, each over one column of every lane's 8. The
+// general kernel below fetches W_dt and delta once per (sequence, channel) quad from L2: 53
+// sequences of 3584 channels, dt_rank 224, took 18.0 us for 28 MB; 9.9 us here.
+template <typename T, int NK, int SPW, int CT>
 __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(ScanArgs a) {
+    constexpr bool BF = sizeof(T) == 2;
     constexpr int NWV = kDtSeqM / SPW;         // waves
     constexpr int KPW = (NK + NWV - 1) / NWV;  // k-chunks per wave
     constexpr int NP = NK < NWV ? NK : NWV;    // partial tiles
@@ -521,7 +532,7 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
     // every wave issues them (waves past the last chunk re-read chunk 0, unused), so that no
     // branch hides the loads' count from the compiler's counter waits
     float4 d0[KPW], d1[KPW];
-    bf16x8 wf[CT][KPW];
+    u32x4 wf[CT][KPW][BF ? 1 : 2];  // 8 bf16, or 8 floats
     {
         const float* drow = a.xdbl + (int64_t)(rok ? tb * kDtSeqM + r : 0) * a.ld_xdbl;
 #pragma unroll
@@ -530,8 +541,11 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
             d0[kk] = *(const float4*)(drow + 32 * k + kq);
             d1[kk] = *(const float4*)(drow + 32 * k + kq + 4);
 #pragma unroll
-            for (int t = 0; t < CT; ++t)
-                wf[t][kk] = *(const bf16x8*)((const bf16*)a.w_dt + (int64_t)((tg * CT + t) * kDtCh + r) * a.R + 32 * k + kq);
+            for (int t = 0; t < CT; ++t) {
+                const T* wp = (const T*)a.w_dt + (int64_t)((tg * CT + t) * kDtCh + r) * a.R + 32 * k + kq;
+                wf[t][kk][0] = *(const u32x4*)wp;
+                if constexpr (!BF) wf[t][kk][1] = *(const u32x4*)(wp + 4);
+            }
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -549,11 +563,20 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
             f32x4 acc = f32x4{};
 #pragma unroll
             for (int kk = 0; kk < KPW; ++kk) {
-                bf16x8 af;
-                af[0] = (bf16)d0[kk].x; af[1] = (bf16)d0[kk].y; af[2] = (bf16)d0[kk].z; af[3] = (bf16)d0[kk].w;
-                af[4] = (bf16)d1[kk].x; af[5] = (bf16)d1[kk].y; af[6] = (bf16)d1[kk].z; af[7] = (bf16)d1[kk].w;
-                if (!rok || wave + NWV * kk >= NK) af = bf16x8{};
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wf[t][kk], acc, 0, 0, 0);
+                const bool kok = rok && wave + NWV * kk < NK;
+                if constexpr (BF) {
+                    bf16x8 af;
+                    af[0] = (bf16)d0[kk].x; af[1] = (bf16)d0[kk].y; af[2] = (bf16)d0[kk].z; af[3] = (bf16)d0[kk].w;
+                    af[4] = (bf16)d1[kk].x; af[5] = (bf16)d1[kk].y; af[6] = (bf16)d1[kk].z; af[7] = (bf16)d1[kk].w;
+                    if (!kok) af = bf16x8{};
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_bit_cast(bf16x8, wf[t][kk][0]), acc, 0, 0, 0);
+                } else if (wave + NWV * kk < NK) {
+                    const float af[8] = {d0[kk].x, d0[kk].y, d0[kk].z, d0[kk].w, d1[kk].x, d1[kk].y, d1[kk].z, d1[kk].w};
+                    const f32x4 w0 = __builtin_bit_cast(f32x4, wf[t][kk][0]), w1 = __builtin_bit_cast(f32x4, wf[t][kk][BF ? 0 : 1]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rok ? af[e] : 0.0f, e < 4 ? w0[e & 3] : w1[e & 3], acc, 0, 0, 0);
+                }
             }
             // lane l holds sequences 4 (l / 16) + j of the tile, channel l % 16
 #pragma unroll
@@ -569,8 +592,8 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
             const int c = (tg * CT + t) * kDtCh + it;
-            u[t][j] = (float)((const bf16*)a.u)[(int64_t)bsq[j] * a.E + c];
-            z[t][j] = (float)((const bf16*)a.z)[(int64_t)bsq[j] * a.ld_z + c];
+            u[t][j] = to_f32(((const T*)a.u)[(int64_t)bsq[j] * a.E + c]);
+            z[t][j] = to_f32(((const T*)a.z)[(int64_t)bsq[j] * a.ld_z + c]);
         }
     }
     __syncthreads();
@@ -586,7 +609,7 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
             float dsum = dt_part[t][0][ts][it];
 #pragma unroll
             for (int k = 1; k < NP; ++k) dsum += dt_part[t][k][ts][it];
-            const float dt = (float)(bf16)dsum;  // stored in bf16 as dt_proj's output
+            const float dt = to_f32(from_f32<T>(dsum));  // as dt_proj's output is stored
             const float delta = softplus_f(dt + bdt);
             const float du = delta * u[t][j];
             const float hv[4] = {h[t][j].x, h[t][j].y, h[t][j].z, h[t][j].w};
@@ -603,12 +626,12 @@ __global__ __launch_bounds__(64 * kDtSeqM / SPW) void decode_dt_ssm_mfma_kernel(
             if (!sok[j]) {
                 if (q == 0) {
                     atomicOr(a.status, SSM_STATUS_BAD_SLOT);
-                    ((bf16*)a.g)[(int64_t)bsq[j] * a.E + c] = (bf16)0.0f;
+                    ((T*)a.g)[(int64_t)bsq[j] * a.E + c] = from_f32<T>(0.0f);
                 }
                 continue;
             }
             ((float4*)(a.pool + ((int64_t)slot[j] * a.E + c) * kN))[q] = make_float4(hn[0], hn[1], hn[2], hn[3]);
-            if (q == 0) ((bf16*)a.g)[(int64_t)bsq[j] * a.E + c] = (bf16)((y + Dc * u[t][j]) * silu_f(z[t][j]));
+            if (q == 0) ((T*)a.g)[(int64_t)bsq[j] * a.E + c] = from_f32<T>((y + Dc * u[t][j]) * silu_f(z[t][j]));
         }
     }
 }
@@ -810,16 +833,19 @@ hipError_t launch_decode_dt_ssm(const ScanArgs& a, bool bf, hipStream_t s) {
     if (a.R % 8 != 0 || a.E % kDtCh != 0 || a.ld_xdbl % 4 != 0 || ((uintptr_t)a.xdbl & 15) != 0 ||
         ((uintptr_t)a.w_dt & 15) != 0)
         return hipErrorNotSupported;
-    if (bf && a.R % 32 == 0 && a.R <= 16 * 32) {
-        // two 16-channel tiles per workgroup: E is a multiple of 64 (checked with the shape)
-        constexpr int CT = 2;
-        if (a.E % (CT * kDtCh) != 0) return hipErrorNotSupported;
+    const bool tiles = bf || (int64_t)((a.nseq + kDtSeq - 1) / kDtSeq) * (a.E / kDtCh) > kDtF32Tiles;
+    if (tiles && a.R % 32 == 0 && a.R <= 16 * 32 && a.E % 32 == 0) {
+        constexpr int CT = 2;  // 16-channel tiles per workgroup
         const dim3 g16((unsigned)(((a.nseq + kDtSeqM - 1) / kDtSeqM) * (a.E / (kDtCh * CT)))), b16(64 * kDtSeqM / kDtSpw);
         switch (a.R / 32) {
-#define SSM_DTM(NK) case NK: SSM_LAUNCH((decode_dt_ssm_mfma_kernel<NK, kDtSpw, CT>), g16, b16, 0, s, a); break;
+#define SSM_DTL(NK)                                                                                     \
+    if (bf) SSM_LAUNCH((decode_dt_ssm_mfma_kernel<bf16, NK, kDtSpw, CT>), g16, b16, 0, s, a);           \
+    else SSM_LAUNCH((decode_dt_ssm_mfma_kernel<float, NK, kDtSpw, CT>), g16, b16, 0, s, a);
+#define SSM_DTM(NK) case NK: SSM_DTL(NK) break;
             SSM_DTM(1) SSM_DTM(2) SSM_DTM(3) SSM_DTM(4) SSM_DTM(5) SSM_DTM(6) SSM_DTM(7) SSM_DTM(8)
             SSM_DTM(9) SSM_DTM(10) SSM_DTM(11) SSM_DTM(12) SSM_DTM(13) SSM_DTM(14) SSM_DTM(15)
-            default: SSM_LAUNCH((decode_dt_ssm_mfma_kernel<16, kDtSpw, CT>), g16, b16, 0, s, a); break;
+            default: SSM_DTL(16) break;
+#undef SSM_DTL
 #undef SSM_DTM
         }
         return hipGetLastError();

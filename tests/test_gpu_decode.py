@@ -85,6 +85,14 @@ def test_decode_f32_wide_shard(batch):
     _decode_batch_case(synth.LayerShape(256, 4096, 16, 64, 4, 2, "f32"), batch, "stress", 15)
 
 
+# fp32 state step on 16 x 16 dt tiles (1024 channels: from 49 sequences): one k-chunk of 32, seven
+# and sixteen, ragged and full last tiles of sequences
+@pytest.mark.parametrize("rank", [32, 224, 512])
+@pytest.mark.parametrize("batch", [49, 64, 97])
+def test_decode_f32_state_tiles(rank, batch):
+    _decode_batch_case(synth.LayerShape(128, 1024, 16, rank, 4, 1, "f32"), batch, "stress", 18)
+
+
 def _decode_batch_case(shape, batch, init, seed, state_tol=None):
     from paper_2602_21144_amd import binding as B
     full = synth.make_layer(shape, seed, stress=(init == "stress"))

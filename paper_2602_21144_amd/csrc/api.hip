@@ -257,26 +257,43 @@ int common_checks(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, int64
 }
 
 // stage bodies (arguments already checked)
+// delta is rounded to bf16 once, so that dt_proj runs on the DMA-fed bf16 tiles
+bool rounds_delta(const ssm_shard_desc_t* d, int64_t T) {
+    return d->act_dtype == SSM_BF16 && d->dt_rank % 32 == 0 && T > 64;
+}
+
+// own: x_dbl stays inside the call (no exchange, no norm of it), so its delta is rounded here too
 int prefill1(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void* x, int64_t T,
-             const ssm_seq_meta_t* m, void* conv_pool, int32_t S, float* xdbl, const PrefillWs& L, hipStream_t s) {
+             const ssm_seq_meta_t* m, void* conv_pool, int32_t S, float* xdbl, const PrefillWs& L, hipStream_t s,
+             bool own = false) {
     const int adt = d->act_dtype;
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state, dm = d->d_model;
     SSM_TRY(gemm(T, 2 * E, dm, x, dm, adt, w->in_proj_w, dm, adt, L.xz, 2 * E, adt, s, "prefill.in_proj", kGemmInProj, L.splitk));
     ConvArgs ca = conv_args(d, w, L.xz, T, m->cu_seqlens, m->cache_slot, m->has_initial_state, m->nseq, conv_pool,
                             S, L.u, L.status);
     SSM_TIMED("prefill.conv1d", s, launch_conv_prefill(ca, adt == SSM_BF16, s));
-    SSM_TIMED("prefill.conv_history", s, launch_conv_state_update(ca, adt == SSM_BF16, s));
-    SSM_TRY(gemm(T, W, E, L.u, E, adt, w->x_proj_w, E, adt, xdbl, W, SSM_F32, s, "prefill.x_proj", kGemmXProj, L.splitk));
+    const int xs = adt == SSM_BF16 ? gemm_bf16_slices(kGemmXProj, T, W, E, true, L.splitk.bytes) : 1;
+    const bool round = own && rounds_delta(d, T);
+    SSM_TRY(gemm(T, W, E, L.u, E, adt, w->x_proj_w, E, adt, xs > 1 ? nullptr : xdbl, W, SSM_F32, s, "prefill.x_proj",
+                 kGemmXProj, L.splitk));
+    if (xs > 1 || round) {
+        const XdblFinish f{L.splitk.p, xs, xdbl, round ? L.delta16 : nullptr, T, (int)W, d->dt_rank};
+        SSM_TIMED("prefill.x_finish", s, launch_xdbl_finish(ca, f, s));
+    } else {
+        SSM_TIMED("prefill.conv_history", s, launch_conv_state_update(ca, adt == SSM_BF16, s));
+    }
     return SSM_OK;
 }
 
+// own: stage 1 has rounded delta. yslices: out_proj may leave K-slices in L.splitk instead of y, and
+// says how many (1: y is written)
 int prefill2(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const float* xdbl, int64_t T,
-             const ssm_seq_meta_t* m, float* ssm_pool, int32_t S, void* y, const PrefillWs& L, hipStream_t s) {
+             const ssm_seq_meta_t* m, float* ssm_pool, int32_t S, void* y, const PrefillWs& L, hipStream_t s,
+             bool own = false, int* yslices = nullptr) {
     const int adt = d->act_dtype;
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state, dm = d->d_model, R = d->dt_rank;
-    if (adt == SSM_BF16 && R % 32 == 0 && T > 64) {
-        // delta is rounded to bf16 once, so dt_proj runs on the DMA-fed bf16 tiles
-        SSM_TIMED("prefill.dt_round", s, launch_round_bf16_rows(xdbl, W, L.delta16, T, (int)R, s));
+    if (rounds_delta(d, T)) {
+        if (!own) SSM_TIMED("prefill.dt_round", s, launch_round_bf16_rows(xdbl, W, L.delta16, T, (int)R, s));
         SSM_TRY(gemm(T, E, R, L.delta16, R, adt, w->dt_proj_w, R, adt, L.dt, E, adt, s, "prefill.dt_proj", kGemmDtProj, L.splitk));
     } else {
         SSM_TRY(gemm(T, E, R, xdbl, W, SSM_F32, w->dt_proj_w, R, adt, L.dt, E, adt, s, "prefill.dt_proj", kGemmDtProj, L.splitk));
@@ -284,8 +301,10 @@ int prefill2(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const floa
     ScanArgs sa = scan_args(d, w, L.u, L.dt, L.xz, xdbl, T, m->cu_seqlens, m->cache_slot, m->has_initial_state,
                             m->nseq, ssm_pool, S, L.g, L.status, L.scan);
     SSM_TRY_HIP(launch_scan_prefill(sa, adt == SSM_BF16, s), "selective scan");
-    SSM_TRY(gemm(T, dm, E, L.g, E, adt, w->out_proj_w, E, adt, y, dm, adt, s, "prefill.out_proj", kGemmOutProj, L.splitk));
-    return SSM_OK;
+    const int ys = yslices && adt == SSM_BF16 ? gemm_bf16_slices(kGemmOutProj, T, dm, E, false, L.splitk.bytes) : 1;
+    if (yslices) *yslices = ys;
+    return gemm(T, dm, E, L.g, E, adt, w->out_proj_w, E, adt, ys > 1 ? nullptr : y, dm, adt, s, "prefill.out_proj",
+                kGemmOutProj, L.splitk);
 }
 
 SkinnyArgs skinny(const void* A, int64_t lda, bool a_f32, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t M,
@@ -576,8 +595,8 @@ int ssm_shard_prefill(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, c
         SSM_TRY(check_ptr(x, "x"));
         SSM_TRY(check_ptr(y, "y_partial"));
     }
-    SSM_TRY(prefill1(d, w, x, T, m, conv_pool, S, L.xdbl, L, s));
-    return prefill2(d, w, L.xdbl, T, m, ssm_pool, S, y, L, s);
+    SSM_TRY(prefill1(d, w, x, T, m, conv_pool, S, L.xdbl, L, s, true));
+    return prefill2(d, w, L.xdbl, T, m, ssm_pool, S, y, L, s, true);
 }
 
 int ssm_shard_decode_stage1(const ssm_shard_desc_t* d, const ssm_shard_weights_t* w, const void* x, int32_t B,
@@ -1332,13 +1351,20 @@ int ssm_stack_prefill(const ssm_stack_desc_t* sd, const ssm_shard_weights_t* lay
     SSM_TIMED("layer.residual_rmsnorm", s,
               launch_residual_rmsnorm(x, bf, none, bf, B.resid, norm_w[0], eps, B.normed, bf, T, dm, s));
     for (int l = 0; l < sd->n_layers; ++l) {
-        SSM_TRY(prefill1(d, &layers[l], B.normed, T, m, conv_pools[l], S, L.xdbl, L, s));
+        const bool own = sd->bcdt_eps <= 0.0f;
+        int ys = 1;
+        SSM_TRY(prefill1(d, &layers[l], B.normed, T, m, conv_pools[l], S, L.xdbl, L, s, own));
         if (sd->bcdt_eps > 0.0f) SSM_TIMED("layer.bcdt_rms", s, launch_bcdt_rms(L.xdbl, T, R, N, W, sd->bcdt_eps, s));
-        SSM_TRY(prefill2(d, &layers[l], L.xdbl, T, m, ssm_pools[l], S, B.y, L, s));
+        SSM_TRY(prefill2(d, &layers[l], L.xdbl, T, m, ssm_pools[l], S, B.y, L, s, own, &ys));
         const bool last = l + 1 == sd->n_layers;
-        SSM_TIMED("layer.residual_rmsnorm", s,
-                  launch_residual_rmsnorm(B.resid, false, one_part(B.y), bf, B.resid, last ? final_w : norm_w[l + 1],
-                                          eps, last ? out : B.normed, bf, T, dm, s));
+        const float* nw = last ? final_w : norm_w[l + 1];
+        void* no = last ? out : B.normed;
+        if (ys > 1)  // the norm adds out_proj's K-slices itself
+            SSM_TIMED("layer.residual_rmsnorm", s,
+                      launch_residual_rmsnorm_slices(B.resid, L.splitk.p, ys, nw, eps, no, T, dm, s));
+        else
+            SSM_TIMED("layer.residual_rmsnorm", s,
+                      launch_residual_rmsnorm(B.resid, false, one_part(B.y), bf, B.resid, nw, eps, no, bf, T, dm, s));
     }
     return SSM_OK;
 }

@@ -184,6 +184,10 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
 // product runs several times faster; gemm_f32_halves_bytes gives the size (monotone in M, 0:
 // never run this way), and with less the product runs on float32 operands.
 size_t gemm_f32_halves_bytes(int64_t M, int64_t N, int64_t K);
+// K-slices that launch_gemm_nt takes for a bf16 in_proj, x_proj or out_proj with that much scratch.
+// Where it is more than one, a null C leaves the partials [slices][M][N] in the scratch, for a
+// caller that adds them itself (in slice order)
+int gemm_bf16_slices(GemmRole role, int64_t M, int64_t N, int64_t K, bool c_f32, size_t scratch_bytes);
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role);
 // the K-slice scratch that a prefill of up to M rows (monotone in M for bf16) and a decode batch
 // of M reserve for such a product (operands of type dt)
@@ -262,6 +266,15 @@ struct ConvArgs {
 };
 hipError_t launch_conv_prefill(const ConvArgs& a, bool bf16_act, hipStream_t s);
 hipError_t launch_conv_state_update(const ConvArgs& a, bool bf16_act, hipStream_t s);
+// What follows a bf16 x_proj, in one launch: the histories of launch_conv_state_update; with
+// slices > 1 x_dbl [T][W] as the sum of x_proj's K-slices part [slices][T][W]; with delta16 set,
+// its first R columns rounded to bf16 rows of R.
+struct XdblFinish {
+    const float* part; int slices;
+    float* xdbl; void* delta16;
+    int64_t T; int W, R;
+};
+hipError_t launch_xdbl_finish(const ConvArgs& a, const XdblFinish& f, hipStream_t s);
 hipError_t launch_conv_decode(const ConvArgs& a, bool bf16_act, hipStream_t s);
 
 struct ScanArgs {
@@ -367,6 +380,9 @@ int residual_rmsnorm_max_dim();
 hipError_t launch_residual_rmsnorm(const void* base, bool base_bf16, const NormParts& parts, bool parts_bf16,
                                    float* resid, const float* w, float eps, void* out, bool out_bf16, int64_t T, int d,
                                    hipStream_t s);
+// the same with n (2 to 8) float32 parts [n][T][d], added in place to the residual, and a bf16 output
+hipError_t launch_residual_rmsnorm_slices(float* resid, const float* parts, int n, const float* w, float eps, void* out,
+                                          int64_t T, int d, hipStream_t s);
 hipError_t launch_bcdt_rms(float* x, int64_t T, int R, int N, int64_t ld, float eps, hipStream_t s);
 
 }  // namespace ssm

@@ -160,10 +160,8 @@ __global__ __launch_bounds__(256) void conv_prefill_kernel(ConvArgs a) {
 // New history of each sequence = last K-1 entries of (old history | its inputs). Runs
 // after the convolution has read the old histories; each thread reads all it needs
 // before writing, so short pieces (fewer than K-1 tokens) keep the right old entries.
-template <typename T, int K>
-__global__ __launch_bounds__(256) void conv_state_update_kernel(ConvArgs a) {
+template <typename T, int K> __device__ __forceinline__ void conv_history(const ConvArgs& a, int64_t gid) {
     const int groups = a.E / kCV;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= (int64_t)a.nseq * groups) return;
     const int s = (int)(gid / groups);
     const int c0 = (int)(gid % groups) * kCV;
@@ -199,6 +197,46 @@ __global__ __launch_bounds__(256) void conv_state_update_kernel(ConvArgs a) {
     for (int i = 0; i < K - 1; ++i)
 #pragma unroll
         for (int c = 0; c < kCV; ++c) hist[c * (K - 1) + i] = from_f32<T>(nh[i][c]);
+}
+
+template <typename T, int K>
+__global__ __launch_bounds__(256) void conv_state_update_kernel(ConvArgs a) {
+    conv_history<T, K>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// The small passes behind x_proj: each is a few MB at most and took the 4 us of a launch, three
+// of them 12.4 of the 126 us of a 2.8B layer's prefill of 391 tokens. The first workgroups write
+// the histories, the others take 4 columns of x_dbl per thread.
+template <typename T, int K>
+__global__ __launch_bounds__(256) void xdbl_finish_kernel(ConvArgs a, XdblFinish f, int hist_blocks) {
+    if ((int)blockIdx.x < hist_blocks) {
+        conv_history<T, K>(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
+        return;
+    }
+    const int64_t i = (int64_t)((int)blockIdx.x - hist_blocks) * 256 + threadIdx.x;
+    const int c4 = (f.slices > 1 ? f.W : f.R) / 4;
+    if (i >= f.T * c4) return;
+    const int64_t t = i / c4;
+    const int c = (int)(i % c4) * 4;
+    float4 v;
+    if (f.slices > 1) {
+        const float* p = f.part + t * f.W + c;
+        const int64_t slice = f.T * f.W;
+        v = *(const float4*)p;
+#pragma unroll 4
+        for (int k = 1; k < f.slices; ++k) {
+            const float4 q = *(const float4*)(p + k * slice);
+            v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+        }
+        *(float4*)(f.xdbl + t * f.W + c) = v;
+    } else {
+        v = *(const float4*)(f.xdbl + t * f.W + c);
+    }
+    if (f.delta16 && c < f.R) {
+        bf16x4 o;
+        o[0] = (bf16)v.x; o[1] = (bf16)v.y; o[2] = (bf16)v.z; o[3] = (bf16)v.w;
+        *(bf16x4*)((bf16*)f.delta16 + t * f.R + c) = o;
+    }
 }
 
 template <typename T, int K>
@@ -245,6 +283,18 @@ hipError_t launch_conv_state_update(const ConvArgs& a, bool bf, hipStream_t s) {
     const int64_t threads = (int64_t)a.nseq * (a.E / kCV);
     if (bf) SSM_CONV_LAUNCH(conv_state_update_kernel, bf16, a, threads, s);
     SSM_CONV_LAUNCH(conv_state_update_kernel, float, a, threads, s);
+}
+hipError_t launch_xdbl_finish(const ConvArgs& a, const XdblFinish& f, hipStream_t s) {
+    const int64_t hist = a.K == 1 ? 0 : ((int64_t)a.nseq * (a.E / kCV) + 255) / 256;
+    const int64_t rows = (f.T * ((f.slices > 1 ? f.W : f.R) / 4) + 255) / 256;
+    if (hist + rows == 0) return hipSuccess;
+    const dim3 grid((unsigned)(hist + rows));
+    switch (a.K) {
+        case 2: SSM_LAUNCH((xdbl_finish_kernel<bf16, 2>), grid, dim3(256), 0, s, a, f, (int)hist); break;
+        case 3: SSM_LAUNCH((xdbl_finish_kernel<bf16, 3>), grid, dim3(256), 0, s, a, f, (int)hist); break;
+        default: SSM_LAUNCH((xdbl_finish_kernel<bf16, 4>), grid, dim3(256), 0, s, a, f, (int)hist); break;
+    }
+    return hipGetLastError();
 }
 hipError_t launch_conv_decode(const ConvArgs& a, bool bf, hipStream_t s) {
     const int64_t threads = (int64_t)a.nseq * (a.E / kCV);

@@ -657,6 +657,7 @@ template <int ROLE, int BM, int BN, int BK, int NS, int WM, int WN, bool CF, boo
 hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
                    int64_t ldc, hipStream_t s, int splits = 1, float* part = nullptr) {
     const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
+    if (splits <= 1 && !C) return hipErrorInvalidValue;
     if (splits <= 1) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, false, false, MB16, FINE, SB>), dim3(tm * tn), dim3(64 * WM * WN), 0, s,
                    (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr, nullptr, nullptr);
@@ -668,6 +669,7 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
                    s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part,
                    nullptr, nullptr);
         if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        if (!C) return hipSuccess;  // the caller takes the partials
         KernelTimer kt("gemm.splitk_reduce", s);
         const int64_t n = M * ((N + 3) / 4);
         SSM_LAUNCH((splitk_reduce_kernel<CF>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const float*)part,
@@ -1102,6 +1104,12 @@ size_t f32_splitk_bytes(int64_t M, int64_t N, int64_t K) {
     return sp > 1 ? (size_t)sp * M * N * 4 : 0;
 }
 }  // namespace
+
+int gemm_bf16_slices(GemmRole role, int64_t M, int64_t N, int64_t K, bool c_f32, size_t scratch_bytes) {
+    if (M <= 64 || N == 0 || K % 64 != 0 || scratch_bytes == 0) return 1;
+    const GemmPlan g = c_f32 ? plan_bf16<true>(role, M, N, K, scratch_bytes) : plan_bf16<false>(role, M, N, K, scratch_bytes);
+    return g.tile < 0 ? 1 : g.slices;
+}
 
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role) {
     // K-slices or halves, one or the other

@@ -318,6 +318,66 @@ def test_stack_decode_few_rows(dm, E, R, bcdt):
             assert_close(host(o), d["out"], TOL["bf16"], f"stack decode of {Bsz}, step {step}")
 
 
+# 600 tokens of a 2048-channel layer: x_proj and out_proj run on K-slices, added by the pass that
+# also writes the conv histories and by the norm; pieces shorter than the conv window, new and
+# continued sequences
+@pytest.mark.parametrize("bcdt,K", [(False, 4), (True, 3), (False, 2), (False, 1)])
+def test_stack_prefill_slices(bcdt, K):
+    from paper_2602_21144_amd import binding as B
+    shape = synth.LayerShape(1024, 2048, 16, 64, K, 1, "bf16")
+    st = synth.make_stack(shape, 2, 70, stress=True)
+    g = GpuStack(shape, st, bcdt, 4)
+    rng = np.random.default_rng(71)
+    layers = _oracle_stack(shape, st)
+    cp, sp = _oracle_pools(shape, 2, 4)
+    slots = np.array([3, 1, 2], np.int32)
+    eps = ol.BCDT_EPS if bcdt else None
+    for lens, init in (([530, 2, 68], [0, 0, 0]), ([1, 597, 2], [1, 0, 1])):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        x = synth.make_tokens(rng, 600, shape.d_model, "bf16")
+        B.ssm_timing_enable(True)
+        out = g.prefill(_dev(x, g.tdt), B.SeqMeta(cu, slots, init, 4))
+        names = B.ssm_timing_collect()
+        B.ssm_timing_enable(False)
+        assert names["prefill.x_finish"][0] == 2 and "prefill.conv_history" not in names
+        ref = ol.stack_prefill(layers, st["norm_w"], st["final_w"], x.astype(np.float64), cu, slots, init, cp, sp,
+                               "bf16", bcdt_eps=eps)
+        cp, sp = ref["conv_pools"], ref["ssm_pools"]
+        assert_close(host(out), ref["out"], TOL["bf16"], "stack prefill")
+        for l in range(2 if K > 1 else 0):
+            assert_close(host(g.conv[l])[slots], cp[l][0][slots], TOL["bf16"], f"layer {l} histories")
+
+
+# x_dbl kept inside one call and passed between the two: the same sums in the same order (600
+# tokens: K-slices of x_proj; 65: none)
+@pytest.mark.parametrize("T", [65, 600, 2049])
+def test_one_call_prefill_is_its_stages(T):
+    from paper_2602_21144_amd import binding as B
+    shape = synth.LayerShape(1024, 2048, 16, 64, 4, 1, "bf16")
+    full = B.upload_weights(synth.make_layer(shape, 72), "bf16")
+    w = B.weights_struct(full)
+    desc = B.make_desc(shape, 0)
+    x = _dev(synth.make_tokens(np.random.default_rng(73), T, 1024, "bf16"), torch.bfloat16)
+    meta = B.SeqMeta(np.array([0, 2, T], np.int32), np.array([1, 0], np.int32), [1, 1], 2)
+    ws = B.workspace(B.prefill_workspace_bytes(desc, T, 2))
+    got = []
+    for staged in (False, True):
+        torch.manual_seed(74)
+        conv = torch.randn(2, 2048, 3, device="cuda").to(torch.bfloat16)
+        ssm = torch.randn(2, 2048, 16, device="cuda")
+        y = torch.empty(T, 1024, dtype=torch.bfloat16, device="cuda")
+        if staged:
+            xdbl = torch.empty(T, shape.w_dbl, device="cuda")
+            B.ssm_shard_prefill_stage1(desc, w, x, meta, conv, xdbl, ws)
+            B.ssm_shard_prefill_stage2(desc, w, xdbl, meta, ssm, y, ws)
+        else:
+            B.ssm_shard_prefill(desc, w, x, meta, conv, ssm, y, ws)
+        got.append((y, conv, ssm))
+    assert B.take_status(ws) == 0
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_decoding_with_and_without_the_cache():
     """The ablation's two ways of generating: prefill + decode steps from the cache, or a
     prefill of the whole prefix for every token. Both match the oracle and each other."""

@@ -956,7 +956,7 @@ M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base) {
     L.u = take((size_t)T * m.Cc * 2);
     L.g = take((size_t)T * m.E * 2);
     L.gn = take((size_t)T * m.E * 2);
-    L.hs = (float*)take((size_t)T * m.H * 4);
+    L.hs = (float*)take((size_t)T * m.H * (call == kM2Decode ? 4 : 8));
     if (call == kM2Prefill) {
         L.win = ssd_window_len(T, (int)m.H);
         L.maxw = ssd_max_windows(T, nseq, L.win);
@@ -1124,8 +1124,8 @@ int ssm2_shard_prefill_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weigh
     p.win = L.win; p.T = T; p.plan = L.plan; p.plan_count = L.count; p.max_windows = L.maxw; p.states = L.states; p.lsum = L.lsum;
     SSM_TRY_HIP(launch_ssd_prefill(p, s), "ssd prefill");
     if (T > 0)
-        SSM_TIMED("m2.prefill.group_sumsq", s, launch_ssd_group_sumsq(L.hs, (int)m.H, (int)(m.r * m.H), m.hpg, (int)m.G,
-                                                                     sumsq_partial, T, s));
+        SSM_TIMED("m2.prefill.group_sumsq", s, launch_ssd_group_sumsq(L.hs, true, (int)m.H, (int)(m.r * m.H), m.hpg,
+                                                                     (int)m.G, sumsq_partial, T, s));
     return SSM_OK;
 }
 
@@ -1177,8 +1177,8 @@ int ssm2_shard_decode_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weight
     SsdPublic p = m2_ssd(m, w, L, ssm_pool, S, L.status);
     p.slot = slot;
     SSM_TIMED("m2.decode.state", s, launch_ssd_decode(p, B, s));
-    SSM_TIMED("m2.decode.group_sumsq", s, launch_ssd_group_sumsq(L.hs, (int)m.H, (int)(m.r * m.H), m.hpg, (int)m.G,
-                                                                sumsq_partial, B, s));
+    SSM_TIMED("m2.decode.group_sumsq", s, launch_ssd_group_sumsq(L.hs, false, (int)m.H, (int)(m.r * m.H), m.hpg,
+                                                                (int)m.G, sumsq_partial, B, s));
     return SSM_OK;
 }
 

@@ -338,7 +338,8 @@ struct SsdPublic {
     int H;                             // heads of the shard
     int h_global0, hpg, g_off;         // first global head, heads per B/C group, local group offset
     const float* dt_bias; const float* A_log; const float* D;
-    void* g; float* hs;                // [T][H*64] gated output; [T][H] sums of g^2 per head
+    void* g; float* hs;                // [T][H*64] gated output; sums of g^2 per head, prefill [2H][T]
+                                       // (one row per half of its channels), decode [B][H]
     float* pool;                       // [S][H][64][128]
     const int32_t* cu; const int32_t* slot; const int32_t* has_init;
     int32_t* status;
@@ -352,7 +353,7 @@ int ssd_max_windows(int64_t T, int nseq, int win);
 size_t ssd_state_bytes(int max_windows, int H);
 hipError_t launch_ssd_prefill(const SsdPublic& p, hipStream_t s);
 hipError_t launch_ssd_decode(const SsdPublic& p, int batch, hipStream_t s);
-hipError_t launch_ssd_group_sumsq(const float* hs, int H, int h_global0, int hpg, int G, float* out, int64_t T,
+hipError_t launch_ssd_group_sumsq(const float* hs, bool prefill, int H, int h_global0, int hpg, int G, float* out, int64_t T,
                                   hipStream_t s);
 hipError_t launch_ssd_norm(const void* g, const float* sumsq, const float* norm_w, void* out, int64_t T, int E, int G,
                            int gsize, int c_global0, float eps, hipStream_t s);

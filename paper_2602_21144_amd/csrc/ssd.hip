@@ -66,7 +66,8 @@ struct SsdArgs {
                                        // (h_global0 + h) / hpg, stored at local group index - g_off
     const float* dt_bias; const float* A_log; const float* D;
     bf16* g;                           // [T][E]
-    float* hs;                         // [T][H] sum over the head's channels of g^2
+    float* hs;                         // sums of g^2 over a head's channels: prefill [2H][T], one row
+                                       // per half of them; decode [B][H]
     float* pool;                       // [S][H][P][N]
     const int32_t* cu; const int32_t* slot; const int32_t* has_init;
     int32_t* status;
@@ -327,34 +328,57 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void s
 }
 
 // ---------------------------------------------------------------- pass B
-// one lane per (head, p, n): walk the windows in plan order
+// One lane per four states (head, p, n .. n + 3) walks the windows in plan order. The states are
+// read and written in place, so a load may not pass the store before it: the windows' plan,
+// decays and states are fetched kLinkW at a time, ahead of those stores (one window at a time,
+// a float per lane: 26.7 us for a ragged batch of 14384 tokens and 40 heads, 20.8 now).
+constexpr int kLinkW = 8;
 __global__ __launch_bounds__(256) void ssd_link_kernel(SsdArgs a) {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (int64_t)a.H * kP * kS) return;
-    const int h = (int)(gid / (kP * kS));
-    const int e = (int)(gid % (kP * kS));
+    if (gid >= (int64_t)a.H * kP * kS / 4) return;
+    const int h = (int)(gid / (kP * kS / 4));
+    const int e = (int)(gid % (kP * kS / 4)) * 4;
     const int nw = *a.plan_count;
-    float carry = 0.0f;
-    for (int w = 0; w < nw; ++w) {
-        const int4 pl = a.plan[w];
-        if (pl.w & kWinFirst) {
-            carry = 0.0f;
-            if (a.has_init[pl.x]) {
-                const int slot = a.slot[pl.x];
-                if (slot >= 0 && slot < a.S) carry = a.pool[((int64_t)slot * a.H + h) * kP * kS + e];
-                else if (e == 0) atomicOr(a.status, SSM_STATUS_BAD_SLOT);
+    const int64_t hs = (int64_t)kP * kS;  // states of a head
+    f32x4 carry = f32x4{};
+    for (int w0 = 0; w0 < nw; w0 += kLinkW) {
+        int seq[kLinkW], flags[kLinkW];
+        float decay[kLinkW];
+        f32x4 local[kLinkW];
+#pragma unroll
+        for (int k = 0; k < kLinkW; ++k) {
+            const int w = min(w0 + k, nw - 1);
+            const int4 pl = a.plan[w];
+            seq[k] = pl.x;
+            flags[k] = pl.w;
+            decay[k] = a.lsum[(int64_t)w * a.H + h];   // (not written for a last window: not used)
+            local[k] = *(const f32x4*)(a.states + ((int64_t)w * a.H + h) * hs + e);
+        }
+#pragma unroll
+        for (int k = 0; k < kLinkW; ++k) {
+            if (w0 + k >= nw) break;
+            if (flags[k] & kWinFirst) {
+                carry = f32x4{};
+                if (a.has_init[seq[k]]) {
+                    const int slot = a.slot[seq[k]];
+                    if (slot >= 0 && slot < a.S) carry = *(const f32x4*)(a.pool + ((int64_t)slot * a.H + h) * hs + e);
+                    else if (e == 0) atomicOr(a.status, SSM_STATUS_BAD_SLOT);
+                }
+            }
+            // the state entering the window
+            *(f32x4*)(a.states + ((int64_t)(w0 + k) * a.H + h) * hs + e) = carry;
+            if (!(flags[k] & kWinLast)) {
+                const float d = __expf(decay[k]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) carry[i] = d * carry[i] + local[k][i];
             }
         }
-        float* st = a.states + ((int64_t)w * a.H + h) * kP * kS + e;
-        const float local = (pl.w & kWinLast) ? 0.0f : *st;
-        *st = carry;  // state entering the window
-        if (!(pl.w & kWinLast)) carry = __expf(a.lsum[(int64_t)w * a.H + h]) * carry + local;
     }
     // empty sequences that start fresh end with a zero state
     for (int s = 0; s < a.nseq; ++s) {
         if (a.cu[s + 1] != a.cu[s] || a.has_init[s]) continue;
         const int slot = a.slot[s];
-        if (slot >= 0 && slot < a.S) a.pool[((int64_t)slot * a.H + h) * kP * kS + e] = 0.0f;
+        if (slot >= 0 && slot < a.S) *(f32x4*)(a.pool + ((int64_t)slot * a.H + h) * hs + e) = f32x4{};
     }
 }
 
@@ -455,6 +479,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void s
         {
             const f32x16& own = nh ? Zp[1] : Zp[0];
             const __amdgpu_buffer_rsrc_t rg = buffer_rsrc(a.g + t0 * a.E, (uint32_t)(nq * a.E * 2));
+            float sq = 0.0f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float4 zo = L.Zx[wave ^ 2][q][lane];
@@ -466,10 +491,21 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void s
                     const float yv = Y[e] + eci * (own[e] + zv[b]) + Dh * (float)Ep.x[q][b];
                     gv[b] = (bf16)(yv * silu_f((float)Ep.z[q][b]));
                 }
+#pragma unroll
+                for (int b = 0; b < 4; ++b) sq += (float)gv[b] * (float)gv[b];
                 __builtin_amdgcn_raw_buffer_store_b64(
                     __builtin_bit_cast(u32x2, gv), rg,
                     (int)((uint32_t)(i * a.E + h * kP + pb + 8 * q + 4 * hh) * 2), 0, 0);
             }
+            // the sums of squares for the gated norm (a pass of their own over g took 14.8 us for
+            // 14384 x 2560; here they cost nothing measurable): the other 16 of this token's 32
+            // channels are in lane l ^ 32. A wave's 32 tokens are one line of hs; its row is kept
+            // in scalar registers, as the kernel has no vector register left
+            sq += __shfl_xor(sq, 32, 64);
+            const int half = __builtin_amdgcn_readfirstlane(wave) & 1;
+            const __amdgpu_buffer_rsrc_t rh = buffer_rsrc(a.hs + (int64_t)(2 * h + half) * a.T + t0, (uint32_t)(nq * 4));
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq), rh,
+                                                  (int)(hh == 0 ? (uint32_t)i * 4 : kOffOutOfRange), 0, 0);
         }
         if (more) epi_load(a, Ep, h, pb, ib, t0 + kQ, nqn, lane);
     }
@@ -478,23 +514,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void s
         if (slot >= 0 && slot < a.S) state_store(a.pool + ((int64_t)slot * a.H + h) * kP * kS, S, wave, lane);
         else if (threadIdx.x == 0) atomicOr(a.status, SSM_STATUS_BAD_SLOT);
     }
-}
-
-// hs[t][h] = sum over the head's 64 channels of g^2: eight lanes per (token, head), each
-// reading 16 consecutive bytes of the [T][H*64] tensor, so a wave reads 1 KB contiguously
-__global__ __launch_bounds__(256) void ssd_head_sumsq_kernel(const bf16* __restrict__ g, int64_t n8,
-                                                             float* __restrict__ hs) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // 8-element piece of g
-    float s = 0.0f;
-    if (i < n8) {
-        const bf16x8 v = *(const bf16x8*)(g + i * 8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += (float)v[e] * (float)v[e];
-    }
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    s += __shfl_xor(s, 4, 64);
-    if (i < n8 && (i & 7) == 0) hs[i >> 3] = s;
 }
 
 // ---------------------------------------------------------------- decode
@@ -568,28 +587,31 @@ __global__ __launch_bounds__(512) void ssd_decode_kernel(SsdArgs a) {
 }
 
 // ---------------------------------------------------------------- norm
-// out[t][k] = sum over the shard's heads in norm group k of hs[t][h] (fixed order)
-// (the norm group of a head is its global B/C group: both span nheads / ngroups heads)
+// out[t][k] = sum over the shard's heads in norm group k of their sums (fixed order)
+// (the norm group of a head is its global B/C group: both span nheads / ngroups heads).
+// R rows of hs per head; row_major: hs is [R H][T] (consecutive tokens share its lines), else [T][R H]
+template <int R, bool ROW_MAJOR>
 __global__ __launch_bounds__(256) void ssd_group_sumsq_kernel(const float* __restrict__ hs, int H, int h_global0,
                                                               int hpg, int G, float* __restrict__ out, int64_t T) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= T * G) return;
     const int64_t t = i / G;
     const int k = (int)(i % G);
-    // the shard's heads in group k are the global heads [k hpg, (k + 1) hpg); blocks of 8
-    // loads go out together and are added in ascending head order
-    const int h0 = max(0, k * hpg - h_global0), h1 = min(H, (k + 1) * hpg - h_global0);
-    const float* r = hs + t * H;
+    // the shard's heads in group k are the global heads [k hpg, (k + 1) hpg); blocks of 16
+    // loads go out together and are added in ascending order
+    const int h0 = R * max(0, k * hpg - h_global0), h1 = R * min(H, (k + 1) * hpg - h_global0);
+    const float* r = ROW_MAJOR ? hs + t : hs + t * R * H;
+    const int64_t st = ROW_MAJOR ? T : 1;
     float s = 0.0f;
     int h = h0;
-    for (; h + 8 <= h1; h += 8) {
-        float v[8];
+    for (; h + 16 <= h1; h += 16) {
+        float v[16];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = r[h + e];
+        for (int e = 0; e < 16; ++e) v[e] = r[(h + e) * st];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s += v[e];
+        for (int e = 0; e < 16; ++e) s += v[e];
     }
-    for (; h < h1; ++h) s += r[h];
+    for (; h < h1; ++h) s += r[h * st];
     out[i] = s;
 }
 
@@ -646,17 +668,12 @@ hipError_t launch_ssd_prefill(const SsdPublic& p, hipStream_t s) {
     }
     {
         KernelTimer kt("prefill.ssd_link", s);
-        const int64_t lanes = (int64_t)a.H * kP * kS;
+        const int64_t lanes = (int64_t)a.H * kP * kS / 4;
         SSM_LAUNCH(ssd_link_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s, a);
     }
     {
         KernelTimer kt("prefill.ssd_main", s);
         SSM_LAUNCH(ssd_main_kernel, grid, dim3(kWG), 0, s, a);
-    }
-    {
-        KernelTimer kt("prefill.ssd_head_sumsq", s);
-        const int64_t n8 = p.T * a.H * (kP / 8);
-        if (n8 > 0) SSM_LAUNCH(ssd_head_sumsq_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, a.g, n8, a.hs);
     }
     return hipGetLastError();
 }
@@ -673,11 +690,12 @@ hipError_t launch_ssd_decode(const SsdPublic& p, int batch, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_ssd_group_sumsq(const float* hs, int H, int h_global0, int hpg, int G, float* out, int64_t T,
-                                  hipStream_t s) {
+hipError_t launch_ssd_group_sumsq(const float* hs, bool prefill, int H, int h_global0, int hpg, int G, float* out,
+                                  int64_t T, hipStream_t s) {
     if (T <= 0) return hipSuccess;
-    SSM_LAUNCH(ssd_group_sumsq_kernel, dim3((unsigned)((T * G + 255) / 256)), dim3(256), 0, s, hs, H, h_global0, hpg,
-               G, out, T);
+    const dim3 grid((unsigned)((T * G + 255) / 256));
+    if (prefill) SSM_LAUNCH((ssd_group_sumsq_kernel<2, true>), grid, dim3(256), 0, s, hs, H, h_global0, hpg, G, out, T);
+    else SSM_LAUNCH((ssd_group_sumsq_kernel<1, false>), grid, dim3(256), 0, s, hs, H, h_global0, hpg, G, out, T);
     return hipGetLastError();
 }
 

@@ -189,6 +189,15 @@ def test_m2_fused_norm_out_proj(P, G, H):
     assert B.ssm_timing_collect()["m2.decode.norm_out_proj"][0] == 3 * P
 
 
+@pytest.mark.parametrize("lens", [[448], [512, 0, 1], [1, 577, 640], [1153, 63, 128]])
+def test_m2_link_batches(lens):
+    """Window counts below, at and above the eight that the link pass fetches at a time, with
+    sequences starting inside a batch, continued and fresh."""
+    sh = synth.Mamba2Shape(128, 16, 64, 128, 2, 4, 2, "bf16")
+    full = synth.make_mamba2_layer(sh, 90 + len(lens), stress=True)
+    _run_case(sh, full, lens, np.array([1, 0, 1][:len(lens)], np.int32), seed=91)
+
+
 def test_m2_many_short_sequences():
     """60 sequences of 0..5 tokens, some continuing: chunks holding many sequence starts and
     ends, then decode steps."""

@@ -975,6 +975,15 @@ M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base) {
     return L;
 }
 
+// With one norm group the gated norm's inverse RMS is one factor per row of out_proj's output. A
+// decode step whose out_proj is one of the few-row kernels (up to 64 rows) stores g times the
+// norm's weight in stage 1, and stage 2 is the product alone, scaled as it is stored: the norm's
+// own launch is saved (37 rows of the 2.7B half shard 43.0 -> 41.1 us, in a captured graph 47.7 ->
+// 45.4; 64 rows 67.5 -> 65.5). Up to 16 rows the streamed out_proj applies
+// the whole norm to its operand. (In a prefill, where the norm is 24 of 844 us, the main pass and
+// the widest out_proj tile have no registers left for it: both spilled.)
+bool m2_scaled(const M2& m, int64_t B) { return m.G == 1 && B > 16 && B <= 64; }
+
 SsdPublic m2_ssd(const M2& m, const ssm2_shard_weights_t* w, const M2Ws& L, float* pool, int S, int32_t* status) {
     SsdPublic p{};
     p.zx = L.zx; p.ld_zx = m.rows; p.u = L.u; p.ld_u = m.Cc;
@@ -1010,6 +1019,12 @@ int m2_stage2(const M2& m, const ssm2_shard_weights_t* w, const float* sumsq, in
         }
         if (e == hipSuccess) return SSM_OK;
         if (e != hipErrorNotSupported) return fail(SSM_E_HIP, "%s: %s", fused_name, hipGetErrorString(e));
+    }
+    if (fused_name && m2_scaled(m, T)) {
+        SkinnyArgs p = skinny(L.g, m.E, false, w->out_proj_w, m.E, y, m.dm, T, m.dm, m.E);
+        p.rs = RowScale{sumsq, (float)m.gsize, 1e-5f};
+        SSM_SKINNY(fused_name, s, p, kSkinnyStoreScaled);
+        return SSM_OK;
     }
     SSM_TIMED(norm_name, s, launch_ssd_norm(L.g, sumsq, w->norm_w, L.gn, T, (int)m.E, (int)m.G, m.gsize,
                                             (int)(m.r * m.E), 1e-5f, s));
@@ -1176,6 +1191,7 @@ int ssm2_shard_decode_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weight
     }
     SsdPublic p = m2_ssd(m, w, L, ssm_pool, S, L.status);
     p.slot = slot;
+    p.norm_w = m2_scaled(m, B) ? w->norm_w : nullptr;
     SSM_TIMED("m2.decode.state", s, launch_ssd_decode(p, B, s));
     SSM_TIMED("m2.decode.group_sumsq", s, launch_ssd_group_sumsq(L.hs, false, (int)m.H, (int)(m.r * m.H), m.hpg,
                                                                 (int)m.G, sumsq_partial, B, s));

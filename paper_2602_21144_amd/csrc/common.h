@@ -173,6 +173,12 @@ __host__ __device__ inline size_t align256(size_t b) { return (b + 255) & ~size_
 enum GemmRole { kGemmGeneric = 0, kGemmInProj = 1, kGemmXProj = 2, kGemmDtProj = 3, kGemmOutProj = 4 };
 // o [M][K] bf16 (dense) = a [M][K] fp32 (row stride lda) rounded to nearest even; K % 8 == 0
 hipError_t launch_round_bf16_rows(const float* a, int64_t lda, void* o, int64_t M, int K, hipStream_t s);
+// A factor per output row: 1 / sqrt(sumsq[m] / gsize + eps), the inverse RMS of a norm over a whole
+// row of A whose weights A already holds (null sumsq: none)
+struct RowScale {
+    const float* sumsq; float gsize, eps;
+    __device__ __forceinline__ float of(float ss) const { return 1.0f / sqrtf(ss / gsize + eps); }
+};
 // scratch: fp32 partials of a split-K run (outputs with fewer tiles than CUs and a long
 // K); gemm_splitk_bytes gives the most a shape can use (0: it is never split), and with less
 // scratch the GEMM runs in fewer slices or unsplit.
@@ -194,7 +200,7 @@ size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, Ge
 size_t gemm_prefill_scratch(int64_t M, int64_t N, int64_t K, int dt);
 size_t gemm_decode_scratch(int64_t M, int64_t N, int64_t K, int dt, GemmRole role);
 // Few-row (decode) GEMM C = A * B^T with a fused epilogue; bf16 weights.
-enum SkinnyEpi { kSkinnyStoreBf16 = 0, kSkinnyStoreF32 = 1, kSkinnyConv = 2, kSkinnyState = 3 };
+enum SkinnyEpi { kSkinnyStoreBf16 = 0, kSkinnyStoreF32 = 1, kSkinnyConv = 2, kSkinnyState = 3, kSkinnyStoreScaled = 4 };
 struct SkinnyArgs {
     const void* A; int64_t lda; bool a_f32;       // A [M][K], bf16 or fp32 (rounded to bf16 on load)
     const bf16* B; int64_t ldb;                   // B [N][K] bf16
@@ -221,6 +227,7 @@ struct SkinnyArgs {
     // to bf16) to resid and writes the sums; the next in_proj reads resid as A, normalised by
     // them with the weights nrm_w and nrm_eps
     float* resid; float* rss; int nrss;
+    RowScale rs;  // kSkinnyStoreScaled: the factor per row of the bf16 output
 };
 hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s);
 // the streamed kernel with the norm prologue above (plain bf16 stores); hipErrorNotSupported
@@ -338,6 +345,7 @@ struct SsdPublic {
     int H;                             // heads of the shard
     int h_global0, hpg, g_off;         // first global head, heads per B/C group, local group offset
     const float* dt_bias; const float* A_log; const float* D;
+    const float* norm_w;               // [H*64]: g is stored times the norm's weight (null: as it is)
     void* g; float* hs;                // [T][H*64] gated output; sums of g^2 per head, prefill [2H][T]
                                        // (one row per half of its channels), decode [B][H]
     float* pool;                       // [S][H][64][128]

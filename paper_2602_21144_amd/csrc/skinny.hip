@@ -26,7 +26,7 @@
 namespace ssm {
 namespace {
 
-enum Epi { kEpiStoreBf16 = 0, kEpiStoreF32 = 1, kEpiConv = 2, kEpiState = 3, kEpiResid = 4 };
+enum Epi { kEpiStoreBf16 = 0, kEpiStoreF32 = 1, kEpiConv = 2, kEpiState = 3, kEpiResid = 4, kEpiStoreScaled = 5 };
 
 // An A fragment as loaded: 8 bf16, or 8 fp32 rounded to bf16 when it enters the MFMA.
 template <bool A_F32> struct ARaw {
@@ -62,6 +62,16 @@ template <> struct ARaw<true> {
 template <int EPI> struct EpiIn {
     __device__ __forceinline__ void load_slot(const SkinnyArgs&, int) {}
     __device__ __forceinline__ void load(const SkinnyArgs&, int, int) {}
+};
+
+// bf16 stores with a factor per row, from the row's sum of squares
+template <> struct EpiIn<kEpiStoreScaled> {
+    float ss;
+    __device__ __forceinline__ void load_slot(const SkinnyArgs&, int) {}
+    __device__ __forceinline__ void load(const SkinnyArgs& p, int m, int) { ss = p.rs.sumsq[m]; }
+    __device__ __forceinline__ void apply(const SkinnyArgs& p, int m, int n, float v) {
+        ((bf16*)p.C)[(int64_t)m * p.ldc + n] = (bf16)(v * p.rs.of(ss));
+    }
 };
 
 __device__ __forceinline__ bool slot_ok(int slot, int S) { return slot >= 0 && slot < S; }
@@ -745,6 +755,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_dtile_kernel(SkinnyArgs p) {
                        (const bf16*)p.conv_w + (int64_t)c * KW, (const bf16*)p.conv_b + c);
         }
     }
+    float rss[EPI == kEpiStoreScaled ? G : 1];
+    if constexpr (EPI == kEpiStoreScaled) {
+#pragma unroll
+        for (int k = 0; k < G; ++k) rss[k] = p.rs.sumsq[min(m0 + er[k], p.M - 1)];
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     const int nall = p.K / kGemvBK;
@@ -848,6 +863,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_dtile_kernel(SkinnyArgs p) {
             *(float4*)o = make_float4(v[0], v[1], v[2], v[3]);
             *(float4*)(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
         } else {
+            if constexpr (EPI == kEpiStoreScaled) {
+                const float sc = p.rs.of(rss[k]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] *= sc;
+            }
             bf16x8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = (bf16)v[e];
@@ -1257,13 +1277,16 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s)
         else SSM_LAUNCH((gemm_skinny_kernel<16, 8, 2, true, kEpiState, 4>), grid, dim3(512), 0, s, p);
         return hipGetLastError();
     }
-    if (epi == kSkinnyStoreBf16 || epi == kSkinnyConv) {
-        const hipError_t e = epi == kSkinnyConv ? launch_dtile_pick<kEpiConv>(p, s) : launch_dtile_pick<kEpiStoreBf16>(p, s);
+    if (epi == kSkinnyStoreBf16 || epi == kSkinnyStoreScaled || epi == kSkinnyConv) {
+        const hipError_t e = epi == kSkinnyConv   ? launch_dtile_pick<kEpiConv>(p, s)
+                             : epi == kSkinnyStoreScaled ? launch_dtile_pick<kEpiStoreScaled>(p, s)
+                                                         : launch_dtile_pick<kEpiStoreBf16>(p, s);
         if (e != hipErrorNotSupported) return e;
     }
     if (use_skinny32(p)) {
         switch (epi) {
             case kSkinnyStoreBf16: return launch_skinny32<kEpiStoreBf16>(p, s);
+            case kSkinnyStoreScaled: return launch_skinny32<kEpiStoreScaled>(p, s);
             case kSkinnyStoreF32: return launch_skinny32<kEpiStoreF32>(p, s);
             case kSkinnyConv: return launch_skinny32<kEpiConv>(p, s);
             default: break;
@@ -1272,6 +1295,7 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s)
     if (const int nw = gemv_waves(p)) {
         switch (epi) {
             case kSkinnyStoreBf16: return launch_gemv<kEpiStoreBf16>(p, nw, s);
+            case kSkinnyStoreScaled: return launch_gemv<kEpiStoreScaled>(p, nw, s);
             case kSkinnyStoreF32: return launch_gemv<kEpiStoreF32>(p, nw, s);
             case kSkinnyConv: return launch_gemv<kEpiConv>(p, nw, s);
             default: break;
@@ -1280,6 +1304,7 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& p, SkinnyEpi epi, hipStream_t s)
     switch (epi) {
         case kSkinnyStoreBf16: return p.a_f32 ? launch_epi<true, kEpiStoreBf16>(p, s) : launch_epi<false, kEpiStoreBf16>(p, s);
         case kSkinnyStoreF32: return p.a_f32 ? launch_epi<true, kEpiStoreF32>(p, s) : launch_epi<false, kEpiStoreF32>(p, s);
+        case kSkinnyStoreScaled: return launch_epi<false, kEpiStoreScaled>(p, s);
         case kSkinnyConv: return launch_epi<false, kEpiConv>(p, s);
         case kSkinnyState: return launch_epi<true, kEpiState>(p, s);
     }

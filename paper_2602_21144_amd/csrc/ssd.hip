@@ -66,6 +66,7 @@ struct SsdArgs {
                                        // (h_global0 + h) / hpg, stored at local group index - g_off
     const float* dt_bias; const float* A_log; const float* D;
     bf16* g;                           // [T][E]
+    const float* norm_w;               // [E] (decode): g is stored times it (null: as it is)
     float* hs;                         // sums of g^2 over a head's channels: prefill [2H][T], one row
                                        // per half of them; decode [B][H]
     float* pool;                       // [S][H][P][N]
@@ -532,6 +533,7 @@ __global__ __launch_bounds__(512) void ssd_decode_kernel(SsdArgs a) {
     const float dtv = (float)zrow[a.dt_col + h], zv = (float)zrow[h * kP + p];
     const float x = (float)urow[h * kP + p];
     const float dtb = a.dt_bias[h], alog = a.A_log[h], Dh = a.D[h];
+    const float nw = a.norm_w ? a.norm_w[h * kP + p] : 1.0f;
     // B_t and C_t at this lane's n: 8-byte loads (b_col, c_col and ld_u are multiples of 8)
     bf16x4 bv[4], cv[4];
 #pragma unroll
@@ -569,7 +571,7 @@ __global__ __launch_bounds__(512) void ssd_decode_kernel(SsdArgs a) {
     const bf16 gv = ok ? (bf16)(y * silu_f(zv)) : (bf16)0.0f;
     float sq = 0.0f;
     if (q == 0) {
-        a.g[(int64_t)b * a.E + h * kP + p] = gv;
+        a.g[(int64_t)b * a.E + h * kP + p] = a.norm_w ? (bf16)((float)gv * nw) : gv;
         sq = (float)gv * (float)gv;
     }
     sq += __shfl_xor(sq, 8, 64);
@@ -685,7 +687,7 @@ hipError_t launch_ssd_decode(const SsdPublic& p, int batch, hipStream_t s) {
     a.dt_col = p.dt_col; a.b_col = p.b_col; a.c_col = p.c_col; a.H = p.H; a.E = p.H * kP;
     a.h_global0 = p.h_global0; a.hpg = p.hpg; a.g_off = p.g_off;
     a.dt_bias = p.dt_bias; a.A_log = p.A_log; a.D = p.D;
-    a.g = (bf16*)p.g; a.hs = p.hs; a.pool = p.pool; a.slot = p.slot; a.status = p.status; a.S = p.S;
+    a.g = (bf16*)p.g; a.norm_w = p.norm_w; a.hs = p.hs; a.pool = p.pool; a.slot = p.slot; a.status = p.status; a.S = p.S;
     SSM_LAUNCH(ssd_decode_kernel, dim3((unsigned)batch, (unsigned)a.H), dim3(512), 0, s, a);
     return hipGetLastError();
 }

@@ -252,6 +252,31 @@ def test_m2_decode_batches(Bd):
             assert_close(host(ssm[r]), sps[r], STATE_TOL, f"states step {step} shard {r}")
 
 
+# one norm group: 17 to 64 rows carry the norm's weight in g and its inverse RMS in out_proj's
+# store, on 16-column, streamed (2048 columns) and 32-column tiles (6144); 16 and 65 beside them
+@pytest.mark.parametrize("dm,P", [(256, 2), (2048, 1), (6144, 1)])
+@pytest.mark.parametrize("Bd", [16, 17, 33, 64, 65])
+def test_m2_decode_one_norm_group(dm, P, Bd):
+    sh = synth.Mamba2Shape(dm, 8 * P, 64, 128, 1, 4, P, "bf16")
+    full = synth.make_mamba2_layer(sh, 41 + Bd, stress=True)
+    rng = np.random.default_rng(Bd)
+    S = Bd + 2
+    slots = rng.permutation(S)[:Bd].astype(np.int32)
+    cp0, sp0 = _rand_pools(rng, sh, S)
+    g = GpuLayer2(sh, full)
+    conv, ssm = g.new_pools(S)
+    for r in range(P):
+        conv[r].copy_(torch.from_numpy(cp0[r]).cuda().to(torch.bfloat16))
+        ssm[r].copy_(torch.from_numpy(sp0[r]).cuda())
+    xt = synth.make_tokens(rng, Bd, dm, "bf16")
+    yd = g.decode(xt, torch.from_numpy(slots).cuda(), conv, ssm)
+    assert g.status_ok(g.dws)
+    _, ydr = o2.tp_decode_step(_f64(full), sh, xt.astype(np.float64), slots, [c.astype(np.float64) for c in cp0],
+                               [c.astype(np.float64) for c in sp0], "bf16")
+    for r in range(P):
+        assert_close(host(yd[r]), ydr[r], TOL["bf16"], f"shard {r}")
+
+
 def test_m2_empty_batch_and_bad_slot():
     from paper_2602_21144_amd import binding as B
     sh = synth.Mamba2Shape(128, 8, 64, 128, 1, 4, 1, "bf16")

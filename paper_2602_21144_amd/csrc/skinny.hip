@@ -1235,13 +1235,17 @@ hipError_t launch_gemv_slices(const SkinnyArgs& p, hipStream_t s) {
 }
 
 bool gemv_resid_fits(const SkinnyArgs& p) { return gemv_waves(p) != 0; }
-// (the residual is float32: twice the activation registers, so up to 5 stages per wave, or 10
-// with at most 8 rows)
+// The residual is float32: more bytes and registers per workgroup than the bf16 operand, so where the
+// projections are long the norm's launch (4.2 us) is the cheaper one. Three layers in a captured
+// graph, with this route against without: K = 768 1.05x at 1 and 8 rows, 1.03x at 16; K = 2560 1.01x
+// at 1 row, 0.99x at 8, and at 10 rows (8 waves of 160 VGPRs: one workgroup per CU instead of two)
+// 0.91x; K = 3584 and 4096 1.00x at 1 and 8. Hence 4 waves (K up to 1280), or up to 5 stages on 8
+// waves (2560) for at most 4 rows.
 bool gemv_rms_fits(const SkinnyArgs& p) {
     SkinnyArgs q = p;
     q.a_f32 = false;
     const int nw = gemv_waves(q);
-    return (nw == 4 || (nw == 8 && (p.K / kGemvBK <= 8 * 5 || p.M <= 8))) && p.lda % 4 == 0 &&
+    return (nw == 4 || (nw == 8 && p.K / kGemvBK <= 8 * 5 && p.M <= 4)) && p.lda % 4 == 0 &&
            (int64_t)p.M * p.lda * 4 < (int64_t)1 << 31;
 }
 
@@ -1260,8 +1264,7 @@ hipError_t launch_gemv_rms_conv(const SkinnyArgs& p, hipStream_t s) {
     const dim3 grid((unsigned)((p.N + 15) / 16)), block(nw * 64);
 #define SSM_GEMV_R(NW, NST, XB) SSM_LAUNCH((gemm_gemv_kernel<NW, NST, XB, kEpiConv, false, true>), grid, block, 0, s, p)
     if (nw == 4) { if (p.M <= 8) SSM_GEMV_R(4, 5, 1); else SSM_GEMV_R(4, 5, 2); }
-    else if (p.K / kGemvBK <= 8 * 5) { if (p.M <= 8) SSM_GEMV_R(8, 5, 1); else SSM_GEMV_R(8, 5, 2); }
-    else SSM_GEMV_R(8, 10, 1);
+    else SSM_GEMV_R(8, 5, 1);
 #undef SSM_GEMV_R
     return hipGetLastError();
 }

@@ -38,9 +38,10 @@ if ROOT not in sys.path:
 METRIC = "selective-scan prefill tokens/s + decode µs/step per shard; % HBM/MFMA peak"
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}     # dense MFMA
-# float32 products of prefill size run as three f16 products on operands held as sums of two f16
-# values: their roof, in float32 flops, is a third of the dense f16 peak
-PEAK_F32_HALVES_TFLOPS = 2500.0 / 3
+# float32 products of prefill size run as six bf16 products on operands split into three bf16 values
+# (small ones, and the sliced x_proj, on the float32 MFMA): their highest roof, in float32 flops, is
+# a sixth of the dense bf16 peak, and all are held against it
+PEAK_F32_PARTS_TFLOPS = 2500.0 / 6
 # VALU issue: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles, 2.4 GHz
 PEAK_VALU_GINSTS = 256 * 4 * 2.4e9 / 4 / 1e9
 
@@ -139,7 +140,7 @@ def kernel_work(sh, kind, n, nseq):
     bf = sh.act == "bf16"
     if kind == "prefill":
         T = n
-        mfma = "mfma" if bf or T <= 64 else "mfma_halves"
+        mfma = "mfma" if bf or T <= 64 else "mfma_parts"
         out = {"prefill.in_proj": (mfma, 2.0 * T * 2 * E * dm),
                "prefill.conv1d": ("hbm", 2 * T * E * s + E * (K + 1) * s),
                "prefill.conv_history": ("hbm", 2 * nseq * E * (K - 1) * s),
@@ -196,7 +197,7 @@ def keep_busy(torch, ms=1.0):
 
 def mfma_peak(roof, act):
     """TFLOP/s of the matrix cores for a roof, None when it is not theirs."""
-    return {"mfma": PEAK_TFLOPS[act], "mfma_halves": PEAK_F32_HALVES_TFLOPS}.get(roof)
+    return {"mfma": PEAK_TFLOPS[act], "mfma_parts": PEAK_F32_PARTS_TFLOPS}.get(roof)
 
 
 def role_of(name):

@@ -249,9 +249,10 @@ int ssm_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int
  * with fewer tiles than the GPU has compute units and a long K may be computed split-K: the
  * K-slices' float32 partials go to scratch (device, the caller's; ssm_gemm_splitk_bytes
  * gives the most that the shape can use, 0 when it uses none) and a second kernel adds
- * them in slice order. Float32 products of prefill size may keep their operands there as sums
- * of f16 halves (no less exact than the float32 tiles). With less scratch than that the product
- * runs in fewer slices or on float32 operands, with none unsplit. */
+ * them in slice order. With less scratch than that the product runs in fewer slices, with
+ * none unsplit. Float32 products of prefill size may run on the bf16 matrix cores, every
+ * operand value as the exact sum of three bf16 values: each product of two values is then off
+ * by less than 2^-25 of itself, beside the float32 rounding of the sums. */
 int ssm_gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int32_t a_dtype, int32_t b_dtype, int32_t role,
                           size_t* bytes);
 int ssm_gemm_nt_role(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int32_t a_dtype, const void* B,

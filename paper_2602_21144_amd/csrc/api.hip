@@ -99,13 +99,12 @@ int check_meta(const ssm_seq_meta_t* m, int64_t T) {
 }
 
 // ------------------------------------------------------------------ workspaces
-// fp32 partials of the projections that run split-K (few tokens), and the f16 halves of float32
-// operands (prefill)
+// fp32 partials of the projections that run split-K (few tokens); parts: float32 products may run on
+// the bf16 cores (prefill)
 struct Scratch {
     float* p = nullptr;
     size_t bytes = 0;
-    void* halves = nullptr;
-    size_t halves_bytes = 0;
+    bool parts = false;
 };
 
 struct PrefillWs {
@@ -141,13 +140,7 @@ PrefillWs prefill_layout(const ssm_shard_desc_t* d, int64_t T, int nseq, void* b
     sk = std::max(sk, gemm_prefill_scratch(T, dm, E, adt));
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
-    if (adt == SSM_F32) {
-        // one product's operands at a time
-        size_t hb = std::max(gemm_f32_halves_bytes(T, 2 * E, dm), gemm_f32_halves_bytes(T, dm, E));
-        hb = std::max(hb, std::max(gemm_f32_halves_bytes(T, W, E), gemm_f32_halves_bytes(T, E, R)));
-        L.splitk.halves = take(hb);
-        L.splitk.halves_bytes = hb;
-    }
+    L.splitk.parts = true;
     L.total = off;
     return L;
 }
@@ -209,8 +202,8 @@ int gemm(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int adt, c
          void* C, int64_t ldc, int cdt, hipStream_t s, const char* what, GemmRole role = kGemmGeneric,
          Scratch sk = Scratch{}) {
     KernelTimer kt(what, s);
-    SSM_TRY_HIP(launch_gemm_nt(M, N, K, A, lda, adt, B, ldb, bdt, C, ldc, cdt, s, role, sk.p, sk.bytes, sk.halves,
-                               sk.halves_bytes), what);
+    SSM_TRY_HIP(launch_gemm_nt(M, N, K, A, lda, adt, B, ldb, bdt, C, ldc, cdt, s, role, sk.p, sk.bytes,
+                               sk.parts), what);
     return SSM_OK;
 }
 
@@ -796,8 +789,7 @@ int ssm_gemm_nt_role(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     Scratch sk;
     sk.p = scratch;
     sk.bytes = scratch ? scratch_bytes : 0;
-    sk.halves = sk.p;  // a product uses one or the other
-    sk.halves_bytes = sk.bytes;
+    sk.parts = true;
     return gemm(M, N, K, A, lda, adt, B, ldb, bdt, C, ldc, cdt, s, "op.gemm", (GemmRole)role, sk);
 }
 

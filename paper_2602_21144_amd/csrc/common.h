@@ -185,11 +185,9 @@ struct RowScale {
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt,
                           const void* B, int64_t ldb, int b_dt, void* C, int64_t ldc, int c_dt,
                           hipStream_t s, GemmRole role, float* scratch = nullptr, size_t scratch_bytes = 0,
-                          void* halves = nullptr, size_t halves_bytes = 0);
-// halves: room for float32 operands as f16 halves (gemm_split.hip), on which a large float32
-// product runs several times faster; gemm_f32_halves_bytes gives the size (monotone in M, 0:
-// never run this way), and with less the product runs on float32 operands.
-size_t gemm_f32_halves_bytes(int64_t M, int64_t N, int64_t K);
+                          bool parts = false);
+// parts: a float32 product may run on the bf16 cores, its operands as sums of three bf16 values
+// (gemm_split.hip); the prefills' do.
 // K-slices that launch_gemm_nt takes for a bf16 in_proj, x_proj or out_proj with that much scratch.
 // Where it is more than one, a null C leaves the partials [slices][M][N] in the scratch, for a
 // caller that adds them itself (in slice order)

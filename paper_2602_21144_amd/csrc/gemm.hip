@@ -182,9 +182,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt(int M, int N, int K,
 // F32: the operands are float32 rows passed as bf16 rows of twice the length (K, lda and
 // ldb in bf16 units); the DMA and the LDS layout only move bytes, and each 16-byte fragment
 // (4 floats along k) feeds four v_mfma_f32_32x32x2_f32 instead of one bf16 MFMA.
-// ea, eb (F32 only, may be null): the rows' and columns' exponents of the split product launched
-// before (gemm_split.hip); only the outputs of marked rows and columns are computed here, and a
-// tile without any returns at once.
 // MB16: 16x16 MFMA blocks. FINE: the second, fully ordered schedule of the k loop. SB (with
 // FINE): one set of weight fragments, each reloaded right after its last MFMA of a substep
 // (the MFMAs run weight block by weight block), which frees registers for wider tiles.
@@ -193,9 +190,7 @@ template <int ROLE, int BM, int BN, int BK, int NS, int WM, int WN, bool C_F32, 
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int K, const bf16* __restrict__ A,
                                                               int64_t lda, const bf16* __restrict__ B, int64_t ldb,
                                                               void* __restrict__ Cp, int64_t ldc, int tiles_m,
-                                                              int tiles_n, float* __restrict__ part,
-                                                              const int32_t* __restrict__ ea = nullptr,
-                                                              const int32_t* __restrict__ eb = nullptr) {
+                                                              int tiles_n, float* __restrict__ part) {
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     // MFMA blocks: 32x32 (bf16 32x32x16 or fp32 32x32x2), or 16x16 (MB16: bf16 16x16x32 or
@@ -238,14 +233,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int 
     const int m0 = tm * BM, n0 = tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
-    if constexpr (F32 && !SPLIT) {
-        if (ea) {
-            bool marked = false;
-            for (int r = tid; r < BM; r += 64 * NW) marked = marked || (m0 + r < M && ea[m0 + r] == kSplitBad);
-            for (int r = tid; r < BN; r += 64 * NW) marked = marked || (n0 + r < N && eb[n0 + r] == kSplitBad);
-            if (!__syncthreads_or(marked)) return;
-        }
-    }
     if constexpr (SPLIT) {
         A += (int64_t)blockIdx.y * K;
         B += (int64_t)blockIdx.y * K;
@@ -553,14 +540,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma(int M, int N, int 
                 if (m >= M || n >= N) continue;
                 const OT* q = st + r * BN + ((cc ^ (r & 7)) * E16);
                 OT* p = out + (int64_t)m * ldo + n;
-                if constexpr (F32 && !SPLIT) {
-                    if (ea) {
-                        const bool row = ea[m] == kSplitBad;
-                        for (int e = 0; e < E16 && n + e < N; ++e)
-                            if (row || eb[n + e] == kSplitBad) p[e] = q[e];
-                        continue;
-                    }
-                }
                 if (vec && n + E16 <= N) {
                     *(u32x4*)p = *(const u32x4*)q;
                 } else {
@@ -660,14 +639,13 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
     if (splits <= 1 && !C) return hipErrorInvalidValue;
     if (splits <= 1) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, false, false, MB16, FINE, SB>), dim3(tm * tn), dim3(64 * WM * WN), 0, s,
-                   (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr, nullptr, nullptr);
+                   (int)M, (int)N, (int)K, (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, nullptr);
         return hipGetLastError();
     }
     // K-slices are built for the tiles that pick_tile slices
     if constexpr (BK == 64 && BM * BN <= 192 * 128 && BM != 96) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, BK, NS, WM, WN, CF, true, false, MB16, FINE, SB>), dim3(tm * tn, splits), dim3(64 * WM * WN), 0,
-                   s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part,
-                   nullptr, nullptr);
+                   s, (int)M, (int)N, (int)(K / splits), (const bf16*)A, lda, (const bf16*)B, ldb, C, ldc, tm, tn, part);
         if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         if (!C) return hipSuccess;  // the caller takes the partials
         KernelTimer kt("gemm.splitk_reduce", s);
@@ -679,28 +657,31 @@ hipError_t run_dma(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
     return hipErrorInvalidValue;
 }
 
+hipError_t reduce_slices_f32(const float* part, int splits, int64_t M, int64_t N, float* C, int64_t ldc, hipStream_t s) {
+    KernelTimer kt("gemm.splitk_reduce", s);
+    const int64_t n4 = M * ((N + 3) / 4);
+    SSM_LAUNCH((splitk_reduce_kernel<true>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, part, splits, (int)M,
+               (int)N, C, ldc);
+    return hipGetLastError();
+}
+
 // float32 operands on the DMA tiles: the rows are moved as bytes, so the kernel sees them as
 // bf16 rows of twice the length (K, lda, ldb doubled); only the MFMAs read them as floats
 template <int ROLE, int BM, int BN, int NS, int WM, int WN, bool MB16 = false>
 hipError_t run_dma_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B, int64_t ldb,
-                       float* C, int64_t ldc, hipStream_t s, const SplitOperands& marks, int splits = 1,
-                       float* part = nullptr) {
+                       float* C, int64_t ldc, hipStream_t s, int splits = 1, float* part = nullptr) {
     const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
     if (splits <= 1) {
         SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, 64, NS, WM, WN, true, false, true, MB16>), dim3(tm * tn), dim3(64 * WM * WN),
                    0, s, (int)M, (int)N, (int)(2 * K), (const bf16*)A, 2 * lda, (const bf16*)B, 2 * ldb, C, ldc, tm,
-                   tn, nullptr, marks.ea, marks.eb);
+                   tn, nullptr);
         return hipGetLastError();
     }
     SSM_LAUNCH((gemm_bf16_dma<ROLE, BM, BN, 64, NS, WM, WN, true, true, true, MB16>), dim3(tm * tn, splits),
                dim3(64 * WM * WN), 0, s, (int)M, (int)N, (int)(2 * K / splits), (const bf16*)A, 2 * lda,
-               (const bf16*)B, 2 * ldb, C, ldc, tm, tn, part, nullptr, nullptr);
+               (const bf16*)B, 2 * ldb, C, ldc, tm, tn, part);
     if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    KernelTimer kt("gemm.splitk_reduce", s);
-    const int64_t n4 = M * ((N + 3) / 4);
-    SSM_LAUNCH((splitk_reduce_kernel<true>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (const float*)part,
-               splits, (int)M, (int)N, C, ldc);
-    return hipGetLastError();
+    return reduce_slices_f32(part, splits, M, N, C, ldc, s);
 }
 
 // bf16 tiles. Which one is fastest depends on how many of them the output gives: an MI355X
@@ -735,8 +716,6 @@ constexpr TileCost kTileCost[kBfTiles] = {
     {256, 320, 1.554f, 0.0f, 6.65f, false}};
 constexpr int kMaxSlices = 8, kMinSliceK = 8;  // K-slices: at most 8, of at least 8 k-tiles each
 constexpr float kLaunchUs = 2.0f;
-// K-slices write float32 partials, and a second kernel adds them (fitted on the same shapes)
-constexpr float kSplitUs = 3.8f, kSplitUsPerMB = 0.36f;
 
 struct GemmPlan {
     int tile;    // BfTile, or -1: the few-row / decode tile kernels
@@ -767,7 +746,7 @@ GemmPlan pick_tile(int64_t M, int64_t N, int64_t K, size_t scratch_bytes) {
         for (int d = 2; d <= kMaxSlices && d * kMinSliceK <= nk && tiles * d <= 288; ++d) {
             const size_t bytes = (size_t)d * M * N * 4;
             if (nk % d != 0 || bytes > scratch_bytes) continue;
-            const float us = tile_us(t, tiles * d, (float)(nk / d)) + kSplitUs + kSplitUsPerMB * (float)bytes * 1e-6f;
+            const float us = tile_us(t, tiles * d, (float)(nk / d)) + split_reduce_us(bytes);
             if (us < best.us) best = GemmPlan{i, d, us};
         }
     }
@@ -798,14 +777,19 @@ F32Tiles f32_tiles(int64_t M, int64_t N) {
     return best;
 }
 
-// time of the float32 tiles: the same model in us (614 GFLOP/s of float32 MFMA per CU), 64x64
-// tiles at half of it
-float f32_us(F32Tiles t, int64_t M, int64_t N, int64_t K) {
-    const int bm[] = {128, 256, 256, 128, 64}, bn[] = {128, 256, 224, 224, 64};
-    const double eff[] = {0.89, 0.91, 0.93, 0.91, 0.50};
+// Time of a float32 product without the bf16 cores, in us: the same model (614 GFLOP/s of float32
+// MFMA per CU) from 256 128x128 tiles on; below that the register-staged 64x64 tiles, one per CU at a
+// time (measured 0.53-0.64 us per 32 k), or two K-slices of 64x64 DMA tiles, two per CU (1.0-1.1 us)
+float f32_us(int64_t M, int64_t N, int64_t K, int slices) {
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    if (slices > 1) return 8.0f + (float)((t64 * slices + 511) / 512) * 1.07f * (float)(K / (32 * slices));
+    if (t128 < 256) return 4.0f + (float)((t64 + 255) / 256) * 0.57f * (float)(K / 32);
+    const int bm[] = {128, 256, 256, 128}, bn[] = {128, 256, 224, 224};
+    const double eff[] = {0.89, 0.91, 0.93, 0.91};
+    const F32Tiles t = f32_tiles(M, N);
     const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
-    const int per_cu = t == kF32Tiles128 || t == kF32Tiles64 ? 2 : 1;
-    const double rounds = t == kF32Tiles64 ? (double)tiles / (256.0 * per_cu) : (double)((tiles + 256 * per_cu - 1) / (256 * per_cu));
+    const int per_cu = t == kF32Tiles128 ? 2 : 1;
+    const double rounds = (double)((tiles + 256 * per_cu - 1) / (256 * per_cu));
     return 5.0f + (float)(rounds * per_cu * bm[t] * bn[t] * 2.0 * K / (eff[t] * 614.4e3));
 }
 
@@ -1112,8 +1096,10 @@ int gemm_bf16_slices(GemmRole role, int64_t M, int64_t N, int64_t K, bool c_f32,
 }
 
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role) {
-    // K-slices or halves, one or the other
-    if (a_dt == SSM_F32 && b_dt == SSM_F32) return std::max(f32_splitk_bytes(M, N, K), gemm_f32_halves_bytes(M, N, K));
+    if (a_dt == SSM_F32 && b_dt == SSM_F32) {
+        const F32Parts g = plan_f32_parts(M, N, K, SIZE_MAX);
+        return std::max(f32_splitk_bytes(M, N, K), g.slices > 1 ? (size_t)g.slices * M * N * 4 : 0);
+    }
     if (M <= 64 || N == 0 || b_dt != SSM_BF16 || a_dt != SSM_BF16 || K % 64 != 0) return 0;
     if (role == kGemmXProj && M <= 512 && N <= 256) return 0;  // few-row kernel or whole tiles
     // the most that a choice of pick_tile's can use
@@ -1129,7 +1115,9 @@ size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, Ge
 }
 
 size_t gemm_prefill_scratch(int64_t M, int64_t N, int64_t K, int dt) {
-    if (dt == SSM_F32) return f32_splitk_bytes(M, N, K);
+    if (dt == SSM_F32)
+        return std::max(f32_splitk_bytes(M, N, K),
+                        M <= 64 ? 0 : std::min((size_t)kPartsSlices * M * N * 4, (size_t)kPartsGrid * 256 * 224 * 4));
     return K % 64 == 0 ? splitk_reserve(M, N) : 0;
 }
 
@@ -1157,7 +1145,7 @@ size_t gemm_decode_scratch(int64_t M, int64_t N, int64_t K, int dt, GemmRole rol
 
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt, const void* B,
                           int64_t ldb, int b_dt, void* C, int64_t ldc, int c_dt, hipStream_t s, GemmRole role,
-                          float* scratch, size_t scratch_bytes, void* halves, size_t halves_bytes) {
+                          float* scratch, size_t scratch_bytes, bool parts) {
     if (M == 0 || N == 0) return hipSuccess;
     if (b_dt == SSM_F32) {
         // up to 64 rows (a decode step): the weight stream in whole lines
@@ -1195,35 +1183,35 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
             const int sp = few ? fit_slices(f32_slices(((M + 63) / 64) * ((N + 63) / 64), K), M, N, scratch_bytes) : 1;
             if (K % kF32BK == 0 && lda % 4 == 0 && ldb % 4 == 0 && al16(A) && al16(B) && al16(C) &&
                 256 * lda * 4 < ((int64_t)1 << 31) && 256 * ldb * 4 < ((int64_t)1 << 31)) {
-                const bool many = tm2 * tn2 >= 256;
-                const F32Tiles t = many && !few ? f32_tiles(M, N) : kF32Tiles64;
-                float* part = sp > 1 ? scratch : nullptr;
                 const float* fA = (const float*)A;
                 const float* fB = (const float*)B;
                 float* fC = (float*)C;
-                // as f16 halves on the f16 cores when that is faster and no less exact: its
-                // distance from float64 is 1.13e-8 sqrt(K) (2-norm, measured over the shapes of
-                // gemm_split.hip), that of these tiles 1.79e-8 sqrt(K / slices), so it is the
-                // smaller up to two slices. The tiles then run behind it for the rows and
-                // columns it left out.
-                SplitOperands marks{};
-                const size_t hb = gemm_f32_halves_bytes(M, N, K);
-                if (hb > 0 && hb <= halves_bytes && sp <= 2 && gemm_f32_split_us(M, N, K) < f32_us(t, M, N, K)) {
-                    const hipError_t e = launch_gemm_f32_split(role, M, N, K, fA, lda, fB, ldb, fC, ldc, halves, s, &marks);
-                    if (e != hipSuccess) return e;
-                    part = nullptr;
+                // on the bf16 cores when that is faster and no further from float64: its distance
+                // is 1.56e-8 sqrt(K / slices) (2-norm, measured on the shapes of gemm_split.hip),
+                // that of the float32 tiles 1.79e-8 sqrt(K / slices)
+                if (parts) {
+                    const F32Parts g = plan_f32_parts(M, N, K, scratch ? scratch_bytes : 0);
+                    if (sp <= 2 && g.slices * 4 >= sp * 3 && g.us < 0.95f * f32_us(M, N, K, sp)) {
+                        float* to = g.slices > 1 ? scratch : fC;
+                        const hipError_t e = launch_gemm_f32_parts(g, role, M, N, K, fA, lda, fB, ldb, to,
+                                                                   g.slices > 1 ? N : ldc, s);
+                        if (e != hipSuccess || g.slices == 1) return e;
+                        return reduce_slices_f32(scratch, g.slices, M, N, fC, ldc, s);
+                    }
                 }
-                const int slices = marks.ea ? 1 : sp;
+                // (few tiles and a K that does not slice: the register-staged tiles below)
+                const F32Tiles t = few ? kF32Tiles64 : f32_tiles(M, N);
+                float* part = sp > 1 ? scratch : nullptr;
 #define SSM_F32_DMA(R)                                                                                         \
     case R:                                                                                                    \
         switch (t) {                                                                                           \
-            case kF32Tiles256: return run_dma_f32<R, 256, 256, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
-            case kF32Tiles256x224: return run_dma_f32<R, 256, 224, 2, 8, 1>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
-            case kF32Tiles128x224: return run_dma_f32<R, 128, 224, 2, 4, 2, true>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
-            case kF32Tiles64: return run_dma_f32<R, 64, 64, 4, 2, 2>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks, slices, part); \
-            default: return run_dma_f32<R, 128, 128, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, marks); \
+            case kF32Tiles256: return run_dma_f32<R, 256, 256, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
+            case kF32Tiles256x224: return run_dma_f32<R, 256, 224, 2, 8, 1>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
+            case kF32Tiles128x224: return run_dma_f32<R, 128, 224, 2, 4, 2, true>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
+            case kF32Tiles64: return run_dma_f32<R, 64, 64, 4, 2, 2>(M, N, K, fA, lda, fB, ldb, fC, ldc, s, sp, part); \
+            default: return run_dma_f32<R, 128, 128, 2, 2, 4>(M, N, K, fA, lda, fB, ldb, fC, ldc, s); \
         }
-                auto tiles = [&]() -> hipError_t {
+                if (few || tm2 * tn2 >= 256) {
                     switch (role) {
                         SSM_F32_DMA(kGemmInProj)
                         SSM_F32_DMA(kGemmXProj)
@@ -1231,14 +1219,6 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
                         SSM_F32_DMA(kGemmOutProj)
                         default: SSM_F32_DMA(kGemmGeneric)
                     }
-                    return hipErrorInvalidValue;
-                };
-                if (!marks.ea) {
-                    // (few tiles and a K that does not slice: the register-staged tiles below)
-                    if (many || few) return tiles();
-                } else {
-                    KernelTimer kt("gemm.f32_marked", s);
-                    return tiles();
                 }
 #undef SSM_F32_DMA
             }

@@ -44,22 +44,20 @@ template <int BK> __device__ __forceinline__ int swz_k(int row, int chunk) {
 
 }  // namespace
 
-// Split float32 operands (gemm_split.hip): the rows of A and B as f16 halves [K / 32][hi 32 |
-// lo 32] and a power of two per row; kSplitBad marks a row that the split does not suit.
-constexpr int kSplitBad = -(1 << 28);
-constexpr float kSplitSmall = 0.25f;  // below it (rows scaled to 2^15) lo may not be a normal f16
-// nonzero values of a row that may lie below it: of normally distributed rows, far fewer do
-__host__ __device__ inline int split_small_limit(int K) { return 4 + K / 64; }
-constexpr int64_t kSplitMaxK = 8192;  // a row is held in the registers of one workgroup
-struct SplitOperands {
-    void *a, *b;       // [M][2K], [N][2K] f16
-    int32_t *ea, *eb;  // [M], [N]
+// Float32 products on the bf16 matrix cores (gemm_split.hip). The plan is the cheapest tile and
+// number of K-slices whose partials fit the scratch (us: its price, 1e30 where it does not apply);
+// the product leaves slice k's sums in C + k M ldc.
+constexpr int kPartsSlices = 8, kPartsGrid = 288;  // K-slices: at most 8, over grids of up to 288 workgroups
+struct F32Parts {
+    int bn, slices;
+    float us;
 };
-// bytes of halves that such a product needs (monotone in M; 0: it is not run this way), its
-// modelled time, and the product itself: every output but those of marked rows and columns.
-// The caller launches the float32 tiles behind it on the exponents it returns.
-float gemm_f32_split_us(int64_t M, int64_t N, int64_t K);
-hipError_t launch_gemm_f32_split(int role, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
-                                 int64_t ldb, float* C, int64_t ldc, void* halves, hipStream_t s, SplitOperands* out);
+F32Parts plan_f32_parts(int64_t M, int64_t N, int64_t K, size_t scratch_bytes);
+hipError_t launch_gemm_f32_parts(const F32Parts& p, int role, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                                 const float* B, int64_t ldb, float* C, int64_t ldc, hipStream_t s);
+
+// us of the pass that adds K-slices: float32 partials written and read again (fitted on the bf16
+// products' shapes)
+inline float split_reduce_us(size_t bytes) { return 3.8f + 0.36f * (float)bytes * 1e-6f; }
 
 }  // namespace ssm

@@ -183,74 +183,116 @@ def test_gemm_bf16_tiles(B, role, M, N, K):
                      f"{role} {M}x{N}x{K} scratch {0 if sc is None else need}")
 
 
-# one shape per tile of the float32 products on f16 halves (64x64, 64x128, 96x128, 128x128, 192x128,
-# 256x128, 192x256, 256x256), ragged in M and N, odd and even numbers of 32-wide stages
-F32_HALVES_SHAPES = [(129, 5123, 320), (391, 2601, 320), (517, 3587, 352), (1499, 2051, 320), (1029, 3589, 96),
-                     (3999, 1543, 128), (2599, 3077, 96), (3999, 3077, 96), (700, 2600, 2560)]
+# float32 products on the bf16 cores: every tile width (128, 160, 192, 224), unsliced and in K-slices,
+# with even and odd numbers of 32-wide stages, ragged in M and N
+F32_PARTS_SHAPES = [(520, 6540, 384), (516, 6730, 352), (193, 4218, 1152), (4292, 201, 1120), (1549, 5000, 128),
+                    (1285, 5894, 96), (148, 5680, 1344), (135, 6219, 1344), (1283, 6735, 192), (1288, 6814, 160),
+                    (338, 5637, 1280), (135, 6251, 1568), (1584, 6934, 256), (2051, 5391, 288), (321, 5554, 1600),
+                    (2982, 648, 1568)]
 
 
-def _f32_pair(B, A, Bm, M, N, K):
-    """The product with the scratch its halves need, and on float32 operands without scratch."""
+def _f32_parts(B, A, Bm):
+    """(the product as a prefill runs it, the same on the float32 tiles), as float64."""
+    M, K = A.shape
+    N = Bm.shape[0]
     Np = (N + 3) // 4 * 4
-    out = []
+    Ad, Bd = _dev(A, torch.float32), _dev(Bm, torch.float32)
     need = B.gemm_splitk_bytes(M, N, K, B.SSM_F32, B.SSM_F32, "in_proj")
-    for scratch in (torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda"), None):
-        C = torch.full((M, Np), float("nan"), dtype=torch.float32, device="cuda")[:, :N]
-        B.ssm_gemm_nt_role(A, Bm, C, "in_proj", scratch)
-        torch.cuda.synchronize()
-        out.append(C.to(torch.float64).cpu().numpy())
-    return out
+    scratch = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda") if need else None
+    C, T = (torch.full((M, Np), float("nan"), dtype=torch.float32, device="cuda")[:, :N] for _ in range(2))
+    B.ssm_gemm_nt_role(Ad, Bd, C, "in_proj", scratch)
+    B.ssm_gemm_nt(Ad, Bd, T)
+    torch.cuda.synchronize()
+    return C.to(torch.float64).cpu().numpy(), T.to(torch.float64).cpu().numpy()
 
 
-@pytest.mark.parametrize("M,N,K", F32_HALVES_SHAPES)
-def test_gemm_f32_halves(B, M, N, K):
-    """Float32 products of prefill size on f16 halves: no further from the float64 product than
-    the float32 tiles, with rows and columns of very different scales (each is scaled on its
-    own) and zero rows. Bound: each product is off by at most 2^-24 (the left-out lo x lo) +
-    2 x 2^-24 (the operands' residuals), and about 3 K / 32 sums are rounded to float32."""
+def _f32_parts_bound(A, Bm):
+    """Largest error of each output, from the sum of |a b| over its products: 2^-25 for what the
+    parts leave out, and 6 float32 roundings per 32 products, at most 2^-24 of the sum of |a b| each,
+    that add up like random ones (twice their root: the largest of some million outputs). Below
+    the smallest normal number half a step is 2^-150, in each K-slice's sum (8 at most) and in theirs."""
+    K = A.shape[1]
+    S = np.abs(A).astype(np.float64) @ np.abs(Bm).astype(np.float64).T
+    return 2.0 ** -24 * (0.5 + 2.0 * np.sqrt(6.0 * K / 32.0)) * S + 9.0 * 2.0 ** -150
+
+
+@pytest.mark.parametrize("M,N,K", F32_PARTS_SHAPES)
+def test_gemm_f32_parts(B, M, N, K):
+    """Every output within the bound, with rows and columns of very different scales and zero
+    rows; and over all of them no further from float64 than the float32 tiles."""
     rng = np.random.default_rng(M + 7 * N + K)
     A = _rnd_host(rng, (M, K), "f32") * np.float32(10.0) ** rng.integers(-30, 30, (M, 1)).astype(np.float32)
     Bm = _rnd_host(rng, (N, K), "f32", 1.0 / np.sqrt(K)) * np.float32(10.0) ** rng.integers(-6, 6, (N, 1)).astype(np.float32)
     A[M // 2] = 0.0
     Bm[N // 3] = 0.0
-    halves, tiles = _f32_pair(B, _dev(A, torch.float32), _dev(Bm, torch.float32), M, N, K)
-    ref = A.astype(np.float64) @ Bm.astype(np.float64).T
-    assert (halves != tiles).any(), "the halves path is expected to run"
-    # each output against the norms of its row and column
-    scale = np.linalg.norm(A.astype(np.float64), axis=1)[:, None] * np.linalg.norm(Bm.astype(np.float64), axis=1)[None]
-    scale[scale == 0.0] = 1.0
-    eh, et = np.abs(halves - ref) / scale, np.abs(tiles - ref) / scale
-    bound = 2.0 ** -24 * (3.0 + np.sqrt(3.0 * K / 32.0))   # random roundings add up as their root
-    assert eh.max() <= 2.0 * bound, f"largest error {eh.max():.3e}, bound {bound:.3e}"
-    assert np.sqrt((eh ** 2).mean()) <= np.sqrt((et ** 2).mean()), "further from float64 than the float32 tiles"
+    parts, tiles = _f32_parts(B, A, Bm)
+    assert (parts != tiles).any(), "this shape is expected to run on the bf16 cores"
+    ref, bound = A.astype(np.float64) @ Bm.astype(np.float64).T, _f32_parts_bound(A, Bm)
+    assert (np.abs(parts - ref) <= bound).all(), (np.abs(parts - ref) / bound).max()
+    # 6 roundings per 32 products against the float32 tiles' 8 or 16; a root mean square over n outputs
+    # is known to 1 / sqrt(2 n), and four times that of both counts as equal
+    ep, et = (np.sqrt((((c - ref) / bound) ** 2).mean()) for c in (parts, tiles))
+    assert ep <= et * (1.0 + 4.0 / np.sqrt(M * N)), f"further from float64 than the float32 tiles: {ep:.5e} {et:.5e}"
 
 
-@pytest.mark.parametrize("M,N,K", [(391, 2601, 320), (3999, 1543, 128), (700, 2600, 2560)])
-def test_gemm_f32_halves_marked_rows(B, M, N, K):
-    """Rows that two f16 halves do not suit: infinities, NaN, values at the top of the range, and
-    a bulk far below the row's largest value (which meets zeros of the other operand). Their
-    outputs come from the float32 tiles, bit for bit, and the others are not touched by them."""
+@pytest.mark.parametrize("M,N,K", [(520, 6540, 384), (321, 5554, 1600)])
+def test_gemm_f32_parts_small_beside_large(B, M, N, K):
+    """Rows of a few small values beside one that is up to 2^120 times as large and meets a zero:
+    the small ones are the whole output. Row by row another size and count, down to subnormal
+    values; and constant rows whose second and third parts are as large as they get."""
+    rng = np.random.default_rng(K)
+    A = np.zeros((M, K), np.float32)
+    Bm = rng.uniform(0.5, 1.0, (N, K)).astype(np.float32)
+    Bm[:, 0] = 0.0
+    for r in range(M):
+        n = [1, 8, 4 + K // 64, 60, K - 1][r % 5]
+        small, large = [(1.0, 20), (1.0, 42), (1.0, 100), (2.0 ** -30, 20), (2.0 ** -60, 60), (2.0 ** -100, 20),
+                        (2.0 ** -120, 100), (2.0 ** -140, 60)][r // 5 % 8]
+        A[r, 1 + rng.permutation(K - 1)[:n]] = (small * rng.uniform(0.5, 1.0, n)).astype(np.float32)
+        A[r, 0] = np.float32(small * 2.0 ** large)
+    A[7] = A[M - 3] = np.float32(float.fromhex("0x1.001ffap+0"))
+    Bm[5, 1:] = np.float32(float.fromhex("0x1.001ffap+0"))
+    parts, tiles = _f32_parts(B, A, Bm)
+    assert (parts != tiles).any(), "this shape is expected to run on the bf16 cores"
+    ref, bound = A.astype(np.float64) @ Bm.astype(np.float64).T, _f32_parts_bound(A[:, 1:], Bm[:, 1:])
+    # equal products are rounded alike at every step: there the roundings add up one by one
+    equal = [7, M - 3]
+    bound[equal, 5] = 2.0 ** -24 * (0.5 + 6.0 * K / 32.0) * ref[equal, 5]
+    over = np.abs(parts - ref) > bound
+    assert not over.any(), (np.argwhere(over)[:5].tolist(), (np.abs(parts - ref) / bound).max())
+
+
+@pytest.mark.parametrize("M,N,K", [(520, 6540, 384), (321, 5554, 1600), (1285, 5894, 96)])
+def test_gemm_f32_parts_out_of_range(B, M, N, K):
+    """Infinities and NaN, values up to the largest float32 and sums near it: the tiles that hold
+    them are computed on float32, with the infinities and NaN of the float64 product rounded to
+    float32; every finite output keeps the bound."""
     rng = np.random.default_rng(M + N)
     A, Bm = _rnd_host(rng, (M, K), "f32"), _rnd_host(rng, (N, K), "f32", 1.0 / np.sqrt(K))
-    clean = A.astype(np.float64) @ Bm.astype(np.float64).T
     A[3, 5], A[M - 1, K - 1] = np.inf, np.nan
-    A[M // 2] *= np.float32(2.0 ** -24)
-    A[M // 2, 0] = 1.0
+    A[4, 6], A[4, 7] = np.inf, -np.inf
     Bm[N - 2, 1] = -np.inf
-    Bm[7] *= np.float32(2.0 ** 100)   # a large scale alone marks nothing
-    Bm[:, 0] = 0.0
-    A[:, 0] = np.where(np.arange(M) == M // 2, np.float32(1.0), np.float32(0.0))
-    halves, tiles = _f32_pair(B, _dev(A, torch.float32), _dev(Bm, torch.float32), M, N, K)
-    for r in (3, M // 2, M - 1):
-        np.testing.assert_array_equal(halves[r], tiles[r])
-    np.testing.assert_array_equal(halves[:, N - 2], tiles[:, N - 2])
-    rows = np.setdiff1d(np.arange(M), [3, M // 2, M - 1])
-    cols = np.setdiff1d(np.arange(N), [N - 2])
-    with np.errstate(invalid="ignore"):
+    Bm[9] = 0.0                                  # inf x 0 is NaN
+    A[M // 2] *= np.float32(2.0 ** 110)          # finite products from values past 2^104
+    A[M // 2 + 1] = np.float32(3.4e38)
+    Bm[N // 2] = 0.0
+    Bm[N // 2, 2] = 1.0
+    A[M // 2 + 2] *= np.float32(2.0 ** 90)       # sums past 2^80
+    parts, tiles = _f32_parts(B, A, Bm)
+    assert (parts != tiles).any(), "this shape is expected to run on the bf16 cores"
+    with np.errstate(invalid="ignore", over="ignore"):
         ref = A.astype(np.float64) @ Bm.astype(np.float64).T
-    got, ref = halves[np.ix_(rows, cols)], ref[np.ix_(rows, cols)]
-    assert np.isfinite(got).all() and np.isfinite(clean).all()
-    assert np.abs((got - ref) / np.maximum(np.linalg.norm(ref, axis=0), 1e-30) * np.sqrt(len(rows))).max() <= 2e-5
+        bound = _f32_parts_bound(A, Bm)
+        ref32 = ref.astype(np.float32).astype(np.float64)
+    # (a sum of products of the largest value may pass it on the way, by the order of the sum)
+    rows = np.arange(M) != M // 2 + 1
+    np.testing.assert_array_equal(np.isnan(parts)[rows], np.isnan(ref32)[rows])
+    inf = np.isinf(ref32) & rows[:, None]
+    np.testing.assert_array_equal(parts[inf], ref32[inf])
+    fin = np.isfinite(ref32) & rows[:, None]
+    assert np.isfinite(parts[fin]).all()
+    assert (np.abs(parts[fin] - ref[fin]) <= bound[fin]).all()
+    assert parts[M // 2 + 1, N // 2] == float(np.float32(3.4e38))
 
 
 F32_SPLITK_SHAPES = [("x_proj", 2048, 256, 3584), ("x_proj", 2000, 256, 3584), ("in_proj", 256, 3072, 768),

@@ -32,11 +32,14 @@ namespace {
 constexpr int kSplitBK = 32;                                   // k per stage: one 128-byte line of every row
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
-// two values rounded to bf16 (in assembly: the compiler rounds one of them a second time where it is
-// taken back to float32)
+// Two values rounded to bf16. The empty assembly hides where the bits come from: the compiler would
+// round one of the values a second time where it is taken back to float32.
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    uint32_t o;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(o) : "v"(a), "v"(b));
+    typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    bf16x2 v;
+    v[0] = (bf16)a; v[1] = (bf16)b;
+    uint32_t o = __builtin_bit_cast(uint32_t, v);
+    asm("" : "+v"(o));
     return o;
 }
 __device__ __forceinline__ float bits_f32(uint32_t b) { return __builtin_bit_cast(float, b); }

@@ -692,7 +692,9 @@ hipError_t run_dma_f32(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
 // N = 80 .. 16384 and K = 384 .. 8192, weights read from memory; a is what a k-tile costs on a
 // CU that holds one tile (6.8 TFLOP/s per CU for 256x320, 4.4 for 128x128, 1.9 for 64x64: bytes
 // moved per flop), b the first loads' latency and the store. The cheapest is within 2% of the
-// best tile on average over those shapes (6% at the 90th percentile). Against the rule before
+// best tile on average over those shapes (6% at the 90th percentile). It knows no memory rate: a product
+// bound by reading A (65536x288x2048, 268 MB) takes longer than its price (100 us, priced 58), and the
+// tile of least price is the fastest there too (the others 105-136). Against the rule before
 // it (128x128 with a 2-deep ring, 256x256, 256x320 when N is a multiple of 320, and the decode
 // tile kernel up to 512 rows): 391x10240x2560 54.7 -> 30.9 us, 391x2560x5120 36.8 -> 25.3,
 // 1024x3584x3584 47.0 -> 32.9, 2048x2560x5120 85.0 -> 56.1, 2048x5120x2560 88.2 -> 52.0,
@@ -716,6 +718,13 @@ constexpr TileCost kTileCost[kBfTiles] = {
     {256, 320, 1.554f, 0.0f, 6.65f, false}};
 constexpr int kMaxSlices = 8, kMinSliceK = 8;  // K-slices: at most 8, of at least 8 k-tiles each
 constexpr float kLaunchUs = 2.0f;
+
+// Past four rounds 256x320 is taken only where it is priced 2.5% under every other tile: a smaller
+// difference is inside the fit's error, and 256x256 is then the faster one (65536x4096x4096, priced
+// 1.8% apart the other way, 1567 us against 1577; 65536x7168x3584 2415 against 2431). On whole rounds the
+// price holds as it is (16384x5120x2560 308 us against 310, 14384x5120x2560 295 against 301,
+// 16384x2560x2560 155 against 178).
+constexpr float kWideGain = 0.975f;
 
 struct GemmPlan {
     int tile;    // BfTile, or -1: the few-row / decode tile kernels
@@ -741,7 +750,7 @@ GemmPlan pick_tile(int64_t M, int64_t N, int64_t K, size_t scratch_bytes) {
         const TileCost& t = kTileCost[i];
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         const float u = tile_us(t, tiles, (float)nk);
-        if (u < best.us) best = GemmPlan{i, 1, u};
+        if (u < best.us * (i == kT256x320 && tiles > 4 * 256 ? kWideGain : 1.0f)) best = GemmPlan{i, 1, u};
         if (!t.split || tiles >= 192) continue;
         for (int d = 2; d <= kMaxSlices && d * kMinSliceK <= nk && tiles * d <= 288; ++d) {
             const size_t bytes = (size_t)d * M * N * 4;

@@ -185,8 +185,9 @@ int ssm_shard_decode_stage2(const ssm_shard_desc_t* desc, const ssm_shard_weight
  * ssm_shard_decode_step, with its workspace taken from a static device array of
  * SSM_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on until the
  * process ends. The call allocates nothing (leave ssm_timing_enable off: timed launches
- * may create events). A batch whose workspace would exceed the array (the size
- * ssm_shard_decode_workspace_bytes reports) returns SSM_E_WORKSPACE and enqueues nothing.
+ * may create events). A batch whose own workspace (at most the size
+ * ssm_shard_decode_workspace_bytes reports, which also serves every smaller batch) would
+ * exceed the array returns SSM_E_WORKSPACE and enqueues nothing.
  * The array is shared by every call on one GPU, and calls that overlap in time on one
  * GPU race; run them on one stream or otherwise in order. Bad device slots still never
  * cause an out-of-range access, but their status bits are not reported here (validate

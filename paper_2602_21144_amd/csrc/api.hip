@@ -107,6 +107,17 @@ struct Scratch {
     bool parts = false;
 };
 
+// The largest K-slice scratch f(m) over m <= M rows: K-slices grow fewer as the tiles grow more, so a
+// call of fewer rows may use more. f rises between multiples of 32 and is 0 from 32768 rows on where it
+// ever falls (256 tiles of 128 rows leave nothing to slice).
+template <typename F> size_t scratch_up_to(int64_t M, F f) {
+    size_t most = f(M);
+    for (int64_t m = 32; m < std::min<int64_t>(M, 32768); m += 32) most = std::max(most, f(m));
+    return most;
+}
+
+// A layout is a call's own, or (serve_fewer) what also holds every call of fewer rows: the size that the
+// workspace queries report.
 struct PrefillWs {
     int32_t* status;
     char *xz, *u, *dt, *g;
@@ -117,7 +128,7 @@ struct PrefillWs {
     size_t total;
 };
 
-PrefillWs prefill_layout(const ssm_shard_desc_t* d, int64_t T, int nseq, void* base) {
+PrefillWs prefill_layout(const ssm_shard_desc_t* d, int64_t T, int nseq, void* base, bool serve_fewer = false) {
     const size_t s = act_bytes(d);
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state;
     PrefillWs L{};
@@ -134,10 +145,11 @@ PrefillWs prefill_layout(const ssm_shard_desc_t* d, int64_t T, int nseq, void* b
     L.scan = take(scan_scratch_bytes(T, (int)E, nseq));
     const int adt = d->act_dtype;
     const int64_t dm = d->d_model, R = d->dt_rank;
-    size_t sk = gemm_prefill_scratch(T, 2 * E, dm, adt);
-    sk = std::max(sk, gemm_prefill_scratch(T, W, E, adt));
-    sk = std::max(sk, gemm_prefill_scratch(T, E, R, adt));
-    sk = std::max(sk, gemm_prefill_scratch(T, dm, E, adt));
+    auto scratch = [&](int64_t t) {
+        const size_t in_x = std::max(gemm_prefill_scratch(t, 2 * E, dm, adt), gemm_prefill_scratch(t, W, E, adt));
+        return std::max({in_x, gemm_prefill_scratch(t, E, R, adt), gemm_prefill_scratch(t, dm, E, adt)});
+    };
+    const size_t sk = serve_fewer ? scratch_up_to(T, scratch) : scratch(T);
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
     L.splitk.parts = true;
@@ -164,7 +176,7 @@ constexpr int kFusedDecodeMax = 64;
 // rows over 32 columns).
 constexpr int kConvEpilogueMax = 512;
 
-DecodeWs decode_layout(const ssm_shard_desc_t* d, int64_t B, void* base) {
+DecodeWs decode_layout(const ssm_shard_desc_t* d, int64_t B, void* base, bool serve_fewer = false) {
     const size_t s = act_bytes(d);
     const int64_t E = d->d_inner_shard, W = d->dt_rank + 2 * d->d_state;
     DecodeWs L{};
@@ -179,12 +191,12 @@ DecodeWs decode_layout(const ssm_shard_desc_t* d, int64_t B, void* base) {
     L.g = take((size_t)B * E * s);
     const int adt = d->act_dtype;
     const int64_t dm = d->d_model;
-    size_t sk = 0;
-    if (B > kFusedDecodeMax) {
-        sk = gemm_decode_scratch(B, 2 * E, dm, adt, kGemmInProj);
-        sk = std::max(sk, gemm_decode_scratch(B, W, E, adt, kGemmXProj));
-        sk = std::max(sk, gemm_decode_scratch(B, dm, E, adt, kGemmOutProj));
-    }
+    auto scratch = [&](int64_t b) -> size_t {
+        if (b <= kFusedDecodeMax) return 0;
+        return std::max({gemm_decode_scratch(b, 2 * E, dm, adt, kGemmInProj), gemm_decode_scratch(b, W, E, adt, kGemmXProj),
+                         gemm_decode_scratch(b, dm, E, adt, kGemmOutProj)});
+    };
+    const size_t sk = serve_fewer ? scratch_up_to(B, scratch) : scratch(B);
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
     L.total = off;
@@ -524,14 +536,14 @@ int ssm_shard_check_meta_host(const int32_t* cu, const int32_t* slot, const int3
 int ssm_shard_prefill_workspace_bytes(const ssm_shard_desc_t* desc, int64_t max_tokens, int32_t max_seqs, size_t* bytes) {
     SSM_TRY(check_desc(desc));
     if (!bytes || max_tokens < 0 || max_tokens > INT32_MAX || max_seqs < 0) return fail(SSM_E_INVAL, "bad size query");
-    *bytes = prefill_layout(desc, max_tokens, max_seqs, nullptr).total;
+    *bytes = prefill_layout(desc, max_tokens, max_seqs, nullptr, true).total;
     return SSM_OK;
 }
 
 int ssm_shard_decode_workspace_bytes(const ssm_shard_desc_t* desc, int32_t max_batch, size_t* bytes) {
     SSM_TRY(check_desc(desc));
     if (!bytes || max_batch < 0) return fail(SSM_E_INVAL, "bad size query");
-    *bytes = decode_layout(desc, max_batch, nullptr).total;
+    *bytes = decode_layout(desc, max_batch, nullptr, true).total;
     return SSM_OK;
 }
 
@@ -938,7 +950,7 @@ struct M2Ws {
 // it), or a decode step's
 enum M2Call { kM2Prefill, kM2PrefillStage2, kM2Decode };
 
-M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base) {
+M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base, bool serve_fewer = false) {
     M2Ws L{};
     char* b = (char*)base;
     size_t off = kWsHeader;
@@ -951,16 +963,19 @@ M2Ws m2_layout(const M2& m, int64_t T, int nseq, M2Call call, void* base) {
     L.hs = (float*)take((size_t)T * m.H * (call == kM2Decode ? 4 : 8));
     if (call == kM2Prefill) {
         L.win = ssd_window_len(T, (int)m.H);
-        L.maxw = ssd_max_windows(T, nseq, L.win);
+        L.maxw = serve_fewer ? ssd_max_windows_up_to(T, nseq, (int)m.H) : ssd_max_windows(T, nseq, L.win);
         L.plan = take((size_t)L.maxw * 16);
         L.count = (int32_t*)take(16);
         L.states = (float*)take(ssd_state_bytes(L.maxw, (int)m.H));
         L.lsum = (float*)take((size_t)L.maxw * m.H * 4);
     }
-    const size_t sk = call == kM2Decode ? std::max(gemm_decode_scratch(T, m.rows, m.dm, SSM_BF16, kGemmInProj),
-                                                   gemm_decode_scratch(T, m.dm, m.E, SSM_BF16, kGemmOutProj))
-                                        : std::max(gemm_prefill_scratch(T, m.rows, m.dm, SSM_BF16),
-                                                   gemm_prefill_scratch(T, m.dm, m.E, SSM_BF16));
+    auto scratch = [&](int64_t t) {
+        return call == kM2Decode ? std::max(gemm_decode_scratch(t, m.rows, m.dm, SSM_BF16, kGemmInProj),
+                                            gemm_decode_scratch(t, m.dm, m.E, SSM_BF16, kGemmOutProj))
+                                 : std::max(gemm_prefill_scratch(t, m.rows, m.dm, SSM_BF16),
+                                            gemm_prefill_scratch(t, m.dm, m.E, SSM_BF16));
+    };
+    const size_t sk = serve_fewer ? scratch_up_to(T, scratch) : scratch(T);
     L.splitk.p = (float*)take(sk);
     L.splitk.bytes = sk;
     L.total = off;
@@ -1038,7 +1053,7 @@ int ssm2_shard_prefill_workspace_bytes(const ssm2_shard_desc_t* d, int64_t max_t
     SSM_TRY(m2_dims(d, &m));
     if (!bytes) return fail(SSM_E_INVAL, "bytes is null");
     if (max_tokens < 0 || max_seqs < 0) return fail(SSM_E_INVAL, "negative size");
-    *bytes = m2_layout(m, max_tokens, max_seqs, kM2Prefill, nullptr).total;
+    *bytes = m2_layout(m, max_tokens, max_seqs, kM2Prefill, nullptr, true).total;
     return SSM_OK;
 }
 
@@ -1047,7 +1062,7 @@ int ssm2_shard_decode_workspace_bytes(const ssm2_shard_desc_t* d, int32_t max_ba
     SSM_TRY(m2_dims(d, &m));
     if (!bytes) return fail(SSM_E_INVAL, "bytes is null");
     if (max_batch < 0) return fail(SSM_E_INVAL, "negative size");
-    *bytes = m2_layout(m, max_batch, 0, kM2Decode, nullptr).total;
+    *bytes = m2_layout(m, max_batch, 0, kM2Decode, nullptr, true).total;
     return SSM_OK;
 }
 
@@ -1319,7 +1334,7 @@ int ssm_stack_prefill_workspace_bytes(const ssm_stack_desc_t* desc, int64_t max_
     if (!desc) return fail(SSM_E_INVAL, "stack desc is null");
     SSM_TRY(check_desc(&desc->layer));
     if (!bytes || max_tokens < 0 || max_tokens > INT32_MAX || max_seqs < 0) return fail(SSM_E_INVAL, "bad size query");
-    const size_t lt = prefill_layout(&desc->layer, max_tokens, max_seqs, nullptr).total;
+    const size_t lt = prefill_layout(&desc->layer, max_tokens, max_seqs, nullptr, true).total;
     *bytes = stack_bufs(&desc->layer, max_tokens, lt, nullptr).total;
     return SSM_OK;
 }
@@ -1328,7 +1343,7 @@ int ssm_stack_decode_workspace_bytes(const ssm_stack_desc_t* desc, int32_t max_b
     if (!desc) return fail(SSM_E_INVAL, "stack desc is null");
     SSM_TRY(check_desc(&desc->layer));
     if (!bytes || max_batch < 0) return fail(SSM_E_INVAL, "bad size query");
-    const size_t lt = decode_layout(&desc->layer, max_batch, nullptr).total;
+    const size_t lt = decode_layout(&desc->layer, max_batch, nullptr, true).total;
     *bytes = stack_bufs(&desc->layer, max_batch, lt, nullptr).total;
     return SSM_OK;
 }

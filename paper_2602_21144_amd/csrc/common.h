@@ -193,8 +193,8 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
 // caller that adds them itself (in slice order)
 int gemm_bf16_slices(GemmRole role, int64_t M, int64_t N, int64_t K, bool c_f32, size_t scratch_bytes);
 size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, GemmRole role);
-// the K-slice scratch that a prefill of up to M rows (monotone in M for bf16) and a decode batch
-// of M reserve for such a product (operands of type dt)
+// the K-slice scratch that a prefill of M rows and a decode batch of M use for such a product
+// (operands of type dt); fewer rows may use more (bf16 prefills: never)
 size_t gemm_prefill_scratch(int64_t M, int64_t N, int64_t K, int dt);
 size_t gemm_decode_scratch(int64_t M, int64_t N, int64_t K, int dt, GemmRole role);
 // Few-row (decode) GEMM C = A * B^T with a fused epilogue; bf16 weights.
@@ -356,6 +356,7 @@ struct SsdPublic {
 };
 int ssd_window_len(int64_t T, int H);
 int ssd_max_windows(int64_t T, int nseq, int win);
+int ssd_max_windows_up_to(int64_t T, int nseq, int H);
 size_t ssd_state_bytes(int max_windows, int H);
 hipError_t launch_ssd_prefill(const SsdPublic& p, hipStream_t s);
 hipError_t launch_ssd_decode(const SsdPublic& p, int batch, hipStream_t s);

@@ -637,15 +637,22 @@ __global__ __launch_bounds__(256) void ssd_norm_kernel(const bf16* __restrict__ 
 
 }  // namespace
 
+// about 1280 (window, head) workgroups: two and a half rounds of the 512 that are
+// resident at once (two per CU); windows are whole chunks, 64 to 2048 tokens
+static int64_t target_windows(int H) { return (1280 + H - 1) / H; }
+
 int ssd_window_len(int64_t T, int H) {
-    // about 1280 (window, head) workgroups: two and a half rounds of the 512 that are
-    // resident at once (two per CU); windows are whole chunks, 64 to 2048 tokens
-    const int64_t target = (1280 + H - 1) / H;
+    const int64_t target = target_windows(H);
     const int64_t chunks = ((T + target - 1) / target + kQ - 1) / kQ;
     return (int)std::min<int64_t>(std::max<int64_t>(chunks, 1), 2048 / kQ) * kQ;
 }
 
 int ssd_max_windows(int64_t T, int nseq, int win) { return (int)((T + win - 1) / win + nseq); }
+
+// the most over calls of up to T tokens: the count falls whenever the windows grow by a chunk
+int ssd_max_windows_up_to(int64_t T, int nseq, int H) {
+    return (int)(std::max(std::min((T + kQ - 1) / kQ, target_windows(H)), (T + 2047) / 2048) + nseq);
+}
 
 size_t ssd_state_bytes(int max_windows, int H) { return (size_t)max_windows * H * kP * kS * 4; }
 

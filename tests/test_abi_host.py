@@ -82,6 +82,70 @@ def test_workspace_sizes_grow_with_tokens(B):
     assert B.decode_workspace_bytes(d, 256) > B.decode_workspace_bytes(d, 1)
 
 
+LAYERS = [dict(), dict(d_model=3584, d_inner_total=7168, d_inner_shard=3584, dt_rank=224, act_dtype=0),
+          dict(d_model=4096, d_inner_total=8192, d_inner_shard=2048, dt_rank=256, shard_count=4),
+          dict(d_inner_shard=1280, shard_count=4), dict(d_inner_shard=5120, shard_count=1, act_dtype=0),
+          dict(d_model=768, d_inner_total=1536, d_inner_shard=1536, dt_rank=48, shard_count=1)]
+ROWS = sorted({m + e for m in (*range(64, 1600, 32), 2048, 2560, 4096, 5120, 16384, 32768, 65536) for e in (0, 1)})
+
+
+@pytest.mark.parametrize("kw", LAYERS)
+def test_workspaces_serve_every_smaller_call(B, kw):
+    """A workspace of the size that a query reports is taken by every call of fewer rows, and the
+    sizes never fall as the rows grow. (The calls pass the workspace check and end at a null input.)"""
+    L, d, fake, n = B.lib(), _desc(B, **kw), 1 << 20, ctypes.c_size_t()
+    w, meta, p = B.Weights(*([fake] * 9)), B.SeqMetaC(fake, fake, fake, 3), ctypes.c_void_p(fake)
+    r = ctypes.byref
+    whole = _desc(B, **{**kw, "d_inner_shard": d.d_inner_total, "shard_count": 1})
+    sd = B.StackDesc(whole, 1, 1e-5, 0.0)
+    one = (ctypes.c_void_p * 1)(fake)
+    ws1 = (B.Weights * 1)(w)
+
+    def size(fn, *a):
+        assert fn(*a, r(n)) == 0
+        return n.value
+
+    cases = {
+        "prefill": (lambda m: size(L.ssm_shard_prefill_workspace_bytes, r(d), m, 3),
+                    lambda m, b: L.ssm_shard_prefill(r(d), r(w), None, m, r(meta), p, p, 4, p, p, b, None)),
+        "decode": (lambda m: size(L.ssm_shard_decode_workspace_bytes, r(d), m),
+                   lambda m, b: L.ssm_shard_decode_step(r(d), r(w), None, m, p, p, p, 4, p, p, b, None)),
+        "stack prefill": (lambda m: size(L.ssm_stack_prefill_workspace_bytes, r(sd), m, 3),
+                          lambda m, b: L.ssm_stack_prefill(r(sd), ws1, one, p, None, m, r(meta), one, one, 4, p, p, b, None)),
+        "stack decode": (lambda m: size(L.ssm_stack_decode_workspace_bytes, r(sd), m),
+                         lambda m, b: L.ssm_stack_decode_step(r(sd), ws1, one, p, None, m, p, one, one, 4, p, p, b, None))}
+    _serves_smaller(cases)
+
+
+def _serves_smaller(cases):
+    for what, (size, call) in cases.items():
+        sizes = [size(m) for m in ROWS]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), what
+        for m in ROWS:
+            assert call(m, 0) == -3, f"{what}: {m} rows without a workspace"
+        for i, m in enumerate(ROWS):
+            # the sizes do not fall, so the next larger query is the tightest
+            assert call(m, sizes[min(i + 1, len(ROWS) - 1)]) == -1, f"{what}: {m} rows in a workspace for more"
+
+
+@pytest.mark.parametrize("nheads,ngroups,count,dm", [(80, 1, 2, 2560), (80, 1, 5, 2560), (128, 8, 1, 4096)])
+def test_mamba2_workspaces_serve_every_smaller_call(B, nheads, ngroups, count, dm):
+    """The same for the Mamba-2 shard, whose scan windows grow in steps."""
+    L, fake, n = B.lib(), 1 << 20, ctypes.c_size_t()
+    d = B.Desc2(dm, nheads, 64, 128, ngroups, 4, 0, count, B.SSM_BF16)
+    w, meta, p, r = B.Weights2(*([fake] * 8)), B.SeqMetaC(fake, fake, fake, 3), ctypes.c_void_p(fake), ctypes.byref
+
+    def size(fn, *a):
+        assert fn(*a, r(n)) == 0
+        return n.value
+
+    _serves_smaller({
+        "prefill": (lambda m: size(L.ssm2_shard_prefill_workspace_bytes, r(d), m, 3),
+                    lambda m, b: L.ssm2_shard_prefill_stage1(r(d), r(w), None, m, r(meta), p, p, 4, p, p, b, None)),
+        "decode": (lambda m: size(L.ssm2_shard_decode_workspace_bytes, r(d), m),
+                   lambda m, b: L.ssm2_shard_decode_stage1(r(d), r(w), None, m, p, p, p, 4, p, p, b, None))})
+
+
 def test_entry_points_reject_before_enqueue(B):
     """Bad arguments return an error code; nothing is launched (there is no GPU here)."""
     L = B.lib()

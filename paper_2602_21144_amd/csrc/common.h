@@ -187,7 +187,7 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
                           hipStream_t s, GemmRole role, float* scratch = nullptr, size_t scratch_bytes = 0,
                           bool parts = false);
 // parts: a float32 product may run on the bf16 cores, its operands as sums of three bf16 values
-// (gemm_split.hip); the prefills' do.
+// (gemm_split.h); the prefills' do.
 // K-slices that launch_gemm_nt takes for a bf16 in_proj, x_proj or out_proj with that much scratch.
 // Where it is more than one, a null C leaves the partials [slices][M][N] in the scratch, for a
 // caller that adds them itself (in slice order)

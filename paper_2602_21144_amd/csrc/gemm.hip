@@ -1196,7 +1196,7 @@ hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_
                 const float* fB = (const float*)B;
                 float* fC = (float*)C;
                 // on the bf16 cores when that is faster and no further from float64: its distance
-                // is 1.56e-8 sqrt(K / slices) (2-norm, measured on the shapes of gemm_split.hip),
+                // is 1.56e-8 sqrt(K / slices) (2-norm, measured on the shapes of gemm_split.h),
                 // that of the float32 tiles 1.79e-8 sqrt(K / slices)
                 if (parts) {
                     const F32Parts g = plan_f32_parts(M, N, K, scratch ? scratch_bytes : 0);

@@ -1,4 +1,4 @@
-// Helpers of the DMA-fed GEMM kernels (gemm.hip, gemm_split.hip).
+// Helpers of the DMA-fed GEMM kernels (gemm.hip, gemm_split.h).
 #pragma once
 #include <utility>
 
@@ -44,9 +44,10 @@ template <int BK> __device__ __forceinline__ int swz_k(int row, int chunk) {
 
 }  // namespace
 
-// Float32 products on the bf16 matrix cores (gemm_split.hip). The plan is the cheapest tile and
+// Float32 products on the bf16 matrix cores (gemm_split.h). The plan is the cheapest tile and
 // number of K-slices whose partials fit the scratch (us: its price, 1e30 where it does not apply);
 // the product leaves slice k's sums in C + k M ldc.
+constexpr int kSplitBK = 32;  // k per stage: one 128-byte line of every row
 constexpr int kPartsSlices = 8, kPartsGrid = 288;  // K-slices: at most 8, over grids of up to 288 workgroups
 struct F32Parts {
     int bn, slices;

@@ -166,7 +166,10 @@ int ssm_shard_prefill_stage2(const ssm_shard_desc_t* desc, const ssm_shard_weigh
 /* ------------------------------------------------------------------- decode
  * One token for each of `batch` sequences, advancing their cached history and state
  * in place (Section IV-A). cache_slot [batch] device int32, distinct.
- *   x_t [batch][d_model] act -> y_partial [batch][d_model] act. */
+ *   x_t [batch][d_model] act -> y_partial [batch][d_model] act.
+ * The one call takes the exchange as the identity, as ssm_shard_prefill does. Its x_dbl stays
+ * inside and may be summed in another order than stage 1's: the same to float32 rounding
+ * (and what follows from it), not bit for bit. */
 int ssm_shard_decode_step(const ssm_shard_desc_t* desc, const ssm_shard_weights_t* w,
                           const void* x_t, int32_t batch, const int32_t* cache_slot,
                           void* conv_pool, float* ssm_pool, int32_t num_slots,
@@ -249,9 +252,10 @@ int ssm_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int
  * generic, 1 in_proj, 2 x_proj, 3 dt_proj, 4 out_proj), as the prefill runs it. Outputs
  * with fewer tiles than the GPU has compute units and a long K may be computed split-K: the
  * K-slices' float32 partials go to scratch (device, the caller's; ssm_gemm_splitk_bytes
- * gives the most that the shape can use, 0 when it uses none) and a second kernel adds
- * them in slice order. With less scratch than that the product runs in fewer slices, with
- * none unsplit. Float32 products of prefill size may run on the bf16 matrix cores, every
+ * gives room enough for the shape, 0 when it takes none; 0 also for a bf16 x_proj of up to
+ * 512 rows and 256 columns, which is about as fast without, yet may use up to 8 slices' partials
+ * where more scratch is passed) and a second kernel adds them in slice order. With less scratch
+ * than that the product runs in fewer slices, with none unsplit. Float32 products of prefill size may run on the bf16 matrix cores, every
  * operand value as the exact sum of three bf16 values: each product of two values is then off
  * by less than 2^-25 of itself, beside the float32 rounding of the sums. */
 int ssm_gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int32_t a_dtype, int32_t b_dtype, int32_t role,

@@ -180,7 +180,7 @@ struct RowScale {
     __device__ __forceinline__ float of(float ss) const { return 1.0f / sqrtf(ss / gsize + eps); }
 };
 // scratch: fp32 partials of a split-K run (outputs with fewer tiles than CUs and a long
-// K); gemm_splitk_bytes gives the most a shape can use (0: it is never split), and with less
+// K); gemm_splitk_bytes gives room enough for a shape (0: it needs none), and with less
 // scratch the GEMM runs in fewer slices or unsplit.
 hipError_t launch_gemm_nt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, int a_dt,
                           const void* B, int64_t ldb, int b_dt, void* C, int64_t ldc, int c_dt,

@@ -1110,7 +1110,7 @@ size_t gemm_splitk_bytes(int64_t M, int64_t N, int64_t K, int a_dt, int b_dt, Ge
         return std::max(f32_splitk_bytes(M, N, K), g.slices > 1 ? (size_t)g.slices * M * N * 4 : 0);
     }
     if (M <= 64 || N == 0 || b_dt != SSM_BF16 || a_dt != SSM_BF16 || K % 64 != 0) return 0;
-    if (role == kGemmXProj && M <= 512 && N <= 256) return 0;  // few-row kernel or whole tiles
+    if (role == kGemmXProj && M <= 512 && N <= 256) return 0;  // the few-row kernel is about as fast
     // the most that a choice of pick_tile's can use
     int most = 1;
     const int64_t nk = K / 64;

@@ -93,6 +93,37 @@ def test_decode_f32_state_tiles(rank, batch):
     _decode_batch_case(synth.LayerShape(128, 1024, 16, rank, 4, 1, "f32"), batch, "stress", 18)
 
 
+# The one-call step keeps x_dbl to itself: bf16, up to 16 sequences, from 3072 channels on it is summed
+# in four K-slices, so that it differs from the stages' by float32 roundings, and a dt by at most a bf16
+# step; everywhere else both run the same kernels, bit for bit.
+@pytest.mark.parametrize("E,batch,act,sliced", [(3072, 1, "bf16", True), (3072, 16, "bf16", True), (3072, 17, "bf16", False),
+                                                (2560, 16, "bf16", False), (3072, 16, "f32", False)])
+def test_decode_step_against_its_stages(E, batch, act, sliced):
+    from paper_2602_21144_amd import binding as B
+    shape = synth.LayerShape(256, E, 16, 32, 4, 1, act)
+    g = GpuLayer(shape, synth.make_layer(shape, 19))
+    rng = np.random.default_rng(E + batch)
+    S = batch + 3
+    slots = torch.from_numpy(rng.permutation(S)[:batch].astype(np.int32)).cuda()
+    x = synth.make_tokens(rng, batch, 256, act)
+    pools = [g.new_pools(S, poison=False) for _ in range(2)]
+    h0 = torch.from_numpy((rng.normal(size=(S, E, 16)) * 0.5).astype(np.float32)).cuda()
+    for _, ssm in pools:
+        ssm[0].copy_(h0)
+    staged = g.decode(x, slots, *pools[0])[0]
+    y = torch.empty_like(staged)
+    ws = B.workspace(B.decode_workspace_bytes(g.desc[0], batch))
+    B.ssm_shard_decode_step(g.desc[0], g.ws_struct[0], g.to_dev(x), slots, pools[1][0][0], pools[1][1][0], y, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(pools[0][0][0], pools[1][0][0]), "conv history"
+    if sliced:
+        assert not torch.equal(pools[0][1][0], pools[1][1][0]), "this shape is expected to run x_proj in K-slices"
+        assert_close(host(pools[1][1][0]), host(pools[0][1][0]), STATE_TOL, "state")
+        assert_close(host(y), host(staged), TOL["bf16"], "y")
+    else:
+        assert torch.equal(pools[0][1][0], pools[1][1][0]) and torch.equal(y, staged)
+
+
 def _decode_batch_case(shape, batch, init, seed, state_tol=None):
     from paper_2602_21144_amd import binding as B
     full = synth.make_layer(shape, seed, stress=(init == "stress"))

@@ -147,24 +147,28 @@ def test_gemm_x_proj_decode_rows(B, M, N, K):
     assert_close(C.to(torch.float64).cpu().numpy(), ref, 1e-5, f"x_proj {M}x{N}x{K}")
 
 
-# (role, M, N, K): one shape per tile of the bf16 tile table, ragged in M and N, and its K-slices
+# (role, M, N, K): products whose K-slices run on the tiles that have them, ragged in M and N: 32x64,
+# 64x64, 64x128, 128x128, 192x128 (bf16 and float32 output), 128x192
+BF16_SLICED_SHAPES = [
+    ("in_proj", 67, 76, 2048), ("out_proj", 701, 140, 2560), ("out_proj", 65, 2052, 4096), ("in_proj", 4999, 76, 2560),
+    ("out_proj", 391, 2564, 5120), ("x_proj", 521, 44, 2048), ("x_proj", 321, 160, 4096), ("x_proj", 673, 160, 4096),
+    ("x_proj", 1345, 160, 4096), ("x_proj", 1347, 288, 8192), ("x_proj", 1926, 288, 8192)]
+# one shape per tile of the bf16 tile table, unsliced
 BF16_TILE_SHAPES = [
     ("in_proj", 67, 76, 192), ("in_proj", 701, 140, 128), ("in_proj", 521, 1804, 64), ("in_proj", 523, 3596, 1024),
     ("in_proj", 521, 3588, 64), ("in_proj", 4999, 780, 64), ("in_proj", 4999, 780, 192), ("in_proj", 2001, 3596, 192),
     ("in_proj", 3001, 2604, 320), ("out_proj", 4999, 1804, 2048), ("in_proj", 2001, 3596, 64), ("out_proj", 4999, 2604, 64),
     ("in_proj", 4999, 3596, 320),
-    # K-slices: 32x64, 64x64, 64x128, 128x128, 192x128 (bf16 and float32 output), 128x192
-    ("in_proj", 67, 76, 2048), ("out_proj", 701, 140, 2560), ("out_proj", 65, 2052, 4096), ("in_proj", 4999, 76, 2560),
-    ("out_proj", 391, 2564, 5120), ("x_proj", 521, 44, 2048), ("x_proj", 321, 160, 4096), ("x_proj", 673, 160, 4096),
-    ("x_proj", 1345, 160, 4096), ("x_proj", 1347, 288, 8192), ("x_proj", 1926, 288, 8192), ("x_proj", 5001, 288, 64),
+    ("x_proj", 5001, 288, 64),
     # dt_proj: 64x64, 128x128 and 256x128 tiles on 32-wide stages
     ("dt_proj", 101, 2564, 160), ("dt_proj", 3001, 2604, 96), ("dt_proj", 16399, 2060, 32), ("dt_proj", 391, 1284, 256)]
 
 
-@pytest.mark.parametrize("role,M,N,K", BF16_TILE_SHAPES)
+@pytest.mark.parametrize("role,M,N,K", BF16_TILE_SHAPES + BF16_SLICED_SHAPES)
 def test_gemm_bf16_tiles(B, role, M, N, K):
-    """Every tile of the bf16 table, unsliced (no scratch) and with the scratch its K-slices may
-    use: both match the float64 product. Tolerance: float32 sums of K products of bf16 values,
+    """Every tile of the bf16 table, unsliced (no scratch) and, given room for 8 slices' partials,
+    sliced where the shape is listed for that (the reduce pass is launched) and unsliced
+    where it is not: both match the float64 product. Tolerance: float32 sums of K products of bf16 values,
     rounded once more to bf16 (half a step is 2^-9) where the output is bf16."""
     rng = np.random.default_rng(M + 5 * N + K)
     c_dt = torch.float32 if role == "x_proj" else torch.bfloat16
@@ -173,14 +177,17 @@ def test_gemm_bf16_tiles(B, role, M, N, K):
     ref = A.astype(np.float64) @ Bm.astype(np.float64).T
     if c_dt == torch.bfloat16:
         ref = om.round_bf16(ref)
-    need = B.gemm_splitk_bytes(M, N, K, B.SSM_BF16, B.SSM_BF16, role)
-    scratch = torch.full((max(need // 4, 1),), float("nan"), dtype=torch.float32, device="cuda") if need else None
-    for sc in ([None, scratch] if need else [None]):
+    for room in (0, 8 * M * N):
+        scratch = torch.full((room,), float("nan"), dtype=torch.float32, device="cuda") if room else None
         C = torch.full((M, N), float("nan"), dtype=c_dt, device="cuda")
-        B.ssm_gemm_nt_role(Ad, Bd, C, role, sc)
+        B.ssm_timing_enable(1, "gemm.splitk_reduce")
+        B.ssm_gemm_nt_role(Ad, Bd, C, role, scratch)
         torch.cuda.synchronize()
+        reduces = B.ssm_timing_collect()
+        B.ssm_timing_enable(0)
+        assert bool(reduces) == (room > 0 and (role, M, N, K) in BF16_SLICED_SHAPES), "not the path this row is for"
         assert_close(C.to(torch.float64).cpu().numpy(), ref, 1e-5 if c_dt == torch.float32 else 8e-3,
-                     f"{role} {M}x{N}x{K} scratch {0 if sc is None else need}")
+                     f"{role} {M}x{N}x{K} scratch {4 * room}")
 
 
 # float32 products on the bf16 cores: every tile width (128, 160, 192, 224), unsliced and in K-slices,

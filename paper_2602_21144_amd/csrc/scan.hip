@@ -476,12 +476,22 @@ __global__ __launch_bounds__(256) void decode_ssm_kernel(ScanArgs a) {
 constexpr int kDtCh = 16, kDtSeq = 4;  // tiles of the fp32 / general state-step kernel
 constexpr int kDtSeqM = 16;            // sequences per tile of the bf16 MFMA state-step kernel
 constexpr int kDtSpw = 2;              // sequences per wave of that kernel
-// float32: the tiles once the general kernel has more workgroups (ceil(nseq / 4) E / 16) than this.
-// Below it one round of small workgroups is the shorter one, above it the re-read rows count:
-// 3584 channels, dt_rank 224: 12 sequences (672) 5.9 us there and 6.1 here, 16 (896) 7.1 and 6.4,
-// 53 18.0 and 9.9; 5120 channels, dt_rank 160: 8 (640) 5.3 and 5.7, 12 (960) 6.2 and 6.0, 256 87
-// and 42; 1280 channels: 32 (640) 4.4 and 5.1, 53 (1120) 5.9 and 5.4.
-constexpr int64_t kDtF32Tiles = 768;
+// float32: the tiles where they are the faster. The general kernel reads W_dt and delta again for every
+// (sequence, channel), so it grows with its workgroups (ceil(nseq / 4) E / 16) and with dt_rank; the tiles
+// take about one time per round of 256 workgroups. us, fitted on 110 shapes (512 to 8192 channels,
+// dt_rank 32 to 256, 4 to 256 sequences), 0.2 us of error each, general against tiles: 3584 channels,
+// dt_rank 224: 12 sequences 7.0 and 7.4, 16 8.1 and 7.5, 48 16.6 and 11.3; 2560, 160: 20 7.0 and 7.4, 32
+// 8.4 and 8.1; 1536, 96: 40 6.2 and 7.1, 64 8.2 and 7.7, 96 (a second round of tiles) 10.3 and 10.8; 1024,
+// 64: 53 5.7 and 7.1; 512, 32: 256 7.5 and 7.9. Ties go to the general kernel. Above dt_rank 256 the other
+// form is a product and a state step of their own, which take longer from 768 of those workgroups on.
+bool f32_state_tiles(int64_t nseq, int64_t E, int R) {
+    const int64_t wg = (nseq + kDtSeq - 1) / kDtSeq * (E / kDtCh);
+    if (R > 256) return wg > 768;
+    const int64_t twg = (nseq + kDtSeqM - 1) / kDtSeqM * (E / (2 * kDtCh));
+    const float general = 3.6f + (float)wg * (0.0016f + 1.42e-5f * (float)R);
+    const float tiles = twg <= 256 ? 6.1f + 0.0075f * (float)twg : 2.3f + 4.1f * (float)((twg + 255) / 256);
+    return tiles < general - 0.1f;
+}
 
 // dt_rank a multiple of 32 (up to 512): a workgroup takes CT tiles of 16 channels
 // (adjacent, so they share the delta rows and B, C) of 16 sequences, SPW sequences per wave
@@ -833,7 +843,7 @@ hipError_t launch_decode_dt_ssm(const ScanArgs& a, bool bf, hipStream_t s) {
     if (a.R % 8 != 0 || a.E % kDtCh != 0 || a.ld_xdbl % 4 != 0 || ((uintptr_t)a.xdbl & 15) != 0 ||
         ((uintptr_t)a.w_dt & 15) != 0)
         return hipErrorNotSupported;
-    const bool tiles = bf || (int64_t)((a.nseq + kDtSeq - 1) / kDtSeq) * (a.E / kDtCh) > kDtF32Tiles;
+    const bool tiles = bf || f32_state_tiles(a.nseq, a.E, a.R);
     if (tiles && a.R % 32 == 0 && a.R <= 16 * 32 && a.E % 32 == 0) {
         constexpr int CT = 2;  // 16-channel tiles per workgroup
         const dim3 g16((unsigned)(((a.nseq + kDtSeqM - 1) / kDtSeqM) * (a.E / (kDtCh * CT)))), b16(64 * kDtSeqM / kDtSpw);

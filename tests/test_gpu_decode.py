@@ -85,8 +85,8 @@ def test_decode_f32_wide_shard(batch):
     _decode_batch_case(synth.LayerShape(256, 4096, 16, 64, 4, 2, "f32"), batch, "stress", 15)
 
 
-# fp32 state step on 16 x 16 dt tiles (1024 channels: from 49 sequences): one k-chunk of 32, seven
-# and sixteen, ragged and full last tiles of sequences
+# fp32 state step on 16 x 16 dt tiles (1024 channels, dt_rank 224 and 512: from 49 sequences, dt_rank 32:
+# the general kernel): seven k-chunks of 32 and sixteen, ragged and full last tiles of sequences
 @pytest.mark.parametrize("rank", [32, 224, 512])
 @pytest.mark.parametrize("batch", [49, 64, 97])
 def test_decode_f32_state_tiles(rank, batch):
@@ -122,6 +122,13 @@ def test_decode_step_against_its_stages(E, batch, act, sliced):
         assert_close(host(y), host(staged), TOL["bf16"], "y")
     else:
         assert torch.equal(pools[0][1][0], pools[1][1][0]) and torch.equal(y, staged)
+
+
+# ... and on both sides of the line between the two kernels at smaller ranks, which is not one batch: the
+# tiles (240, 125, 85 sequences: one k-chunk, two, four, the last with a ragged tile) grow by rounds
+@pytest.mark.parametrize("rank,batch", [(32, 240), (32, 321), (64, 97), (64, 125), (128, 61), (128, 85)])
+def test_decode_f32_state_small_ranks(rank, batch):
+    _decode_batch_case(synth.LayerShape(128, 1024, 16, rank, 4, 1, "f32"), batch, "stress", 20)
 
 
 def _decode_batch_case(shape, batch, init, seed, state_tol=None):

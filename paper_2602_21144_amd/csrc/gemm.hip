@@ -869,7 +869,25 @@ hipError_t dispatch_dma(const GemmPlan& g, int64_t M, int64_t N, int64_t K, cons
 // each other's first loads. 64x64 tiles while they fit two rounds (256x3584x224 5.9 -> 4.1 us,
 // 256x2560x160 5.2 -> 3.6), 256x128 ones once they fill four rounds (16384x8192x256 103 -> 96,
 // 65536x2560x160 129 -> 113, 65536x3584x224 205 -> 176 us against 128x128 with a 3-deep ring),
-// 128x128 between (2048x3584x224 9.9 -> 9.1).
+// 128x128 between (2048x3584x224 9.9 -> 9.1). Over long rows of 4 KB this is not so at K = 256
+// (65536x2048x256 119 us against 115 on 256x256 tiles, while 65536x1024 takes 45 against 48 and 65536x4096
+// 207 against 213).
+//
+// Two kinds of K of whole 64-wide tiles do better with those (372 shapes, M = 65 .. 32768, K = 64 .. 256):
+// outputs that give the few-row kernel one round of 32x32 tiles (2.7-2.9 us at K = 64 .. 256 against
+// 3.0-3.8), from K = 192 on also of 64x32 (3.4-3.6 against 3.5-3.9); and from K = 192 on outputs that fill
+// one round of 256x256 tiles (K = 256: 224 .. 256 tiles 13.9-15.1 us against 15.1-16.7, 192 tiles 13.3-13.5
+// against 13.0-13.1; K = 192: 12.8-13.9 against 13.1-14.5).
+bool dt_few_rows(int64_t M, int64_t N, int64_t K) {
+    const int64_t tm64 = (M + 63) / 64, tn32 = (N + 31) / 32;
+    if (!decode_tiles(M, N, K) || (M > 128 && tm64 * ((N + 63) / 64) >= 128)) return false;
+    return tm64 * tn32 < 128 || (K >= 192 && tm64 * tn32 <= 256);
+}
+bool dt_one_round(int64_t M, int64_t N, int64_t K) {
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+    return K % 64 == 0 && K >= 192 && tiles > 204 && tiles <= 256;
+}
+
 template <int ROLE, bool CF>
 hipError_t dispatch_dma32(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                           void* C, int64_t ldc, hipStream_t s) {
@@ -1072,6 +1090,11 @@ hipError_t dispatch_bf16(int64_t M, int64_t N, int64_t K, const void* A, int64_t
             return dispatch_dma<ROLE, CF>(g, M, N, K, A, lda, B, ldb, C, ldc, s, scratch);
         }
         if (ROLE == kGemmXProj && xproj_decode_skinny(M, N)) return few_rows();
+        if constexpr (ROLE == kGemmDtProj) {
+            if (dt_few_rows(M, N, K)) return few_rows();
+            if (dt_one_round(M, N, K))
+                return run_dma<ROLE, 256, 256, 64, 2, 2, 4, CF, true, true>(M, N, K, A, lda, B, ldb, C, ldc, s);
+        }
         if (K % 32 == 0) return dispatch_dma32<ROLE, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
     }
     // staged path: fp32 A (rounded while staging) or a K tail; short K favours more tiles

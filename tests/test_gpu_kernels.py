@@ -161,7 +161,9 @@ BF16_TILE_SHAPES = [
     ("in_proj", 4999, 3596, 320),
     ("x_proj", 5001, 288, 64),
     # dt_proj: 64x64, 128x128 and 256x128 tiles on 32-wide stages
-    ("dt_proj", 101, 2564, 160), ("dt_proj", 3001, 2604, 96), ("dt_proj", 16399, 2060, 32), ("dt_proj", 391, 1284, 256)]
+    ("dt_proj", 101, 2564, 160), ("dt_proj", 3001, 2604, 96), ("dt_proj", 16399, 2060, 32), ("dt_proj", 391, 1284, 256),
+    # ... the few-row kernel's tiles, and 256x256 ones
+    ("dt_proj", 365, 516, 64), ("dt_proj", 99, 4092, 256), ("dt_proj", 3333, 4084, 256), ("dt_proj", 1797, 8188, 192)]
 
 
 @pytest.mark.parametrize("role,M,N,K", BF16_TILE_SHAPES + BF16_SLICED_SHAPES)

@@ -1126,10 +1126,10 @@ int ssm2_shard_prefill_stage1(const ssm2_shard_desc_t* d, const ssm2_shard_weigh
     if (T > 0) {
         SSM_TRY(check_ptr(x, "x"));
         SSM_TRY(check_ptr(sumsq_partial, "sumsq_partial"));
-        // [z ‖ x] and [B ‖ C ‖ dt] as two products: the 2E columns fill whole 256-wide tiles,
-        // and the few others run on narrower tiles instead of a mostly empty last tile column
-        // (for 16384 tokens of the 2.7B half shard: 5 rounds of tiles plus a small product,
-        // where the 5416 columns at once took 6 rounds)
+        // [z ‖ x] and [B ‖ C ‖ dt] as two products: the 2E columns fill whole tiles (256x320: four
+        // rounds for 16384 tokens of the 2.7B half shard), and the few others run on narrower tiles
+        // instead of a mostly empty last tile column: 302 + 30 us, the 5416 columns at once 361.
+        // Not so where that column still fits the last round: 14384 tokens 290 + 29 and 301 us.
         const int64_t nzx = 2 * m.E, nbc = m.rows - nzx;
         SSM_TRY(gemm(T, nzx, m.dm, x, m.dm, SSM_BF16, w->in_proj_w, m.dm, SSM_BF16, L.zx, m.rows, SSM_BF16, s,
                      "m2.prefill.in_proj", kGemmInProj, L.splitk));

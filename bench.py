@@ -42,6 +42,9 @@ PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}     # dense MFMA
 # (small ones, and the sliced x_proj, on the float32 MFMA): their highest roof, in float32 flops, is
 # a sixth of the dense bf16 peak, and all are held against it
 PEAK_F32_PARTS_TFLOPS = 2500.0 / 6
+# the breakdown step times every 15th launch of a kernel name: an odd stride, since some names go
+# over two sizes in turn (gemm.splitk_reduce: x_proj's and out_proj's slices)
+SAMPLE = 15
 # VALU issue: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles, 2.4 GHz
 PEAK_VALU_GINSTS = 256 * 4 * 2.4e9 / 4 / 1e9
 
@@ -366,7 +369,7 @@ def launches_per_step(wl):
 
 
 def measure(B, torch, wl, steps, warmup, dominant_every=None):
-    """Warm-up steps; one breakdown step with every 16th launch of each kernel name timed (the
+    """Warm-up steps; one breakdown step with every SAMPLE-th launch of each kernel name timed (the
     first included) by events bound to its own dispatch; then the timed steps with events at
     every phase boundary and the dominant kernel's dispatches timed by their own events (every
     launch if it runs 200 us or more, else every 16th). A dispatch's events read its execution
@@ -378,15 +381,15 @@ def measure(B, torch, wl, steps, warmup, dominant_every=None):
     torch.cuda.synchronize()
     keep_busy(torch, 20.0)
     B.ssm_timing_collect()
-    B.ssm_timing_enable(True, None, every=16)
+    B.ssm_timing_enable(True, None, every=SAMPLE)
     wl.step()
     torch.cuda.synchronize()
     B.ssm_timing_enable(False)
     sampled = B.ssm_timing_collect()
     per_step = launches_per_step(wl)
     # per kernel name: (launches per step, average ms of its sampled launches)
-    # (names outside kernel_work: about 16 launches for every one sampled)
-    breakdown = {k: (per_step.get(k, 16 * n), ms / n) for k, (n, ms) in sampled.items()}
+    # (names outside kernel_work: about SAMPLE launches for every one sampled)
+    breakdown = {k: (per_step.get(k, SAMPLE * n), ms / n) for k, (n, ms) in sampled.items()}
     dominant = max(breakdown, key=lambda k: breakdown[k][0] * breakdown[k][1])
     dom_avg_ms = breakdown[dominant][1]
     every = dominant_every or (1 if dom_avg_ms >= 0.2 else 16)
@@ -437,7 +440,7 @@ def kernel_figures(wl, m):
         role = role_of(name)
         if role in m["work"] and role == name:
             roof, amts = m["work"][role]
-            sampled = amts[::16]
+            sampled = amts[::SAMPLE]
             rate = (sum(sampled) / len(sampled)) / (ms * 1e-3)
             mf_peak = mfma_peak(roof, sh.act)
             if mf_peak:
@@ -451,7 +454,7 @@ def kernel_figures(wl, m):
     # VALU issue rate from the committed counter summary, when it matches the source
     scan = [k for k in bd if k.startswith("prefill.scan_")]
     if scan and "prefill.scan" in m["work"]:
-        amts = m["work"]["prefill.scan"][1][::16]    # the sampled prefill calls
+        amts = m["work"]["prefill.scan"][1][::SAMPLE]    # the sampled prefill calls
         ms = sum(bd[k][1] for k in scan) * len(amts)
         launches = len(amts)
         amt = sum(amts)

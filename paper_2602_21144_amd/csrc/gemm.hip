@@ -719,12 +719,14 @@ constexpr TileCost kTileCost[kBfTiles] = {
 constexpr int kMaxSlices = 8, kMinSliceK = 8;  // K-slices: at most 8, of at least 8 k-tiles each
 constexpr float kLaunchUs = 2.0f;
 
-// Past four rounds 256x320 is taken only where it is priced 2.5% under every other tile: a smaller
-// difference is inside the fit's error, and 256x256 is then the faster one (65536x4096x4096, priced
-// 1.8% apart the other way, 1567 us against 1577; 65536x7168x3584 2415 against 2431). On whole rounds the
-// price holds as it is (16384x5120x2560 308 us against 310, 14384x5120x2560 295 against 301,
-// 16384x2560x2560 155 against 178).
-constexpr float kWideGain = 0.975f;
+// Past four rounds the two widest tiles are set against each other by whole rounds, 256x320 priced 4%
+// higher: those grids stay in step (all workgroups take the same time), and its price comes out low there.
+// 256x256 against 256x320, us: 65536x4096x4096 1567 and 1577 (16 rounds, 13); 32768x5376x2688 743 and 763
+// (11, 9); 14384x10240x5120 1118 and 1170 (9, 8); 65536x2560x2560 684 and 696 (10, 8); 16384x10240x5120
+// 1285 and 1245 (10, 8); 20480x5120x2560 429 and 404 (7, 5); 40000x5120x2560 857 and 822 (13, 10). Up to four
+// rounds the price holds as it is (16384x5120x2560 310 and 308, 14384x5120x2560 301 and 295, 16384x2560x2560
+// 178 and 155).
+constexpr float kWidePrice = 1.04f;
 
 struct GemmPlan {
     int tile;    // BfTile, or -1: the few-row / decode tile kernels
@@ -750,7 +752,14 @@ GemmPlan pick_tile(int64_t M, int64_t N, int64_t K, size_t scratch_bytes) {
         const TileCost& t = kTileCost[i];
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         const float u = tile_us(t, tiles, (float)nk);
-        if (u < best.us * (i == kT256x320 && tiles > 4 * 256 ? kWideGain : 1.0f)) best = GemmPlan{i, 1, u};
+        bool less = u < best.us;
+        if (i == kT256x320 && tiles > 4 * 256) {
+            const TileCost& q = kTileCost[kT256x256];
+            const int64_t r = (tiles + 255) / 256, rq = (((M + 255) / 256) * ((N + 255) / 256) + 255) / 256;
+            less = best.tile == kT256x256 ? kWidePrice * (float)r * (t.a * (float)nk + t.b) < (float)rq * (q.a * (float)nk + q.b)
+                                          : kWidePrice * u < best.us;
+        }
+        if (less) best = GemmPlan{i, 1, u};
         if (!t.split || tiles >= 192) continue;
         for (int d = 2; d <= kMaxSlices && d * kMinSliceK <= nk && tiles * d <= 288; ++d) {
             const size_t bytes = (size_t)d * M * N * 4;

@@ -817,16 +817,20 @@ float f32_us(int64_t M, int64_t N, int64_t K, int slices) {
 bool decode_tiles(int64_t M, int64_t N, int64_t K) {
     return K % 64 == 0 && M > 64 && M <= 512 && ((M + 31) / 32) * ((N + 31) / 32) >= 128;
 }
-// ... and its price in pick_tile's terms: the tile that launch_dtile_pick takes, fitted on the
-// same shapes (64x64: 104 shapes within 7%). It wins up to about 256 rows over outputs that
-// give one round of its tiles (80x2560x2560 9.1 us against 11.0 on the DMA tiles, 200x3584x3584
-// 15.4 against 17.1; 391x2560x2560 19.2 against 15.9).
+// ... and its price in pick_tile's terms: the tile that launch_dtile_pick takes, fitted on 191 shapes
+// (66 .. 512 rows, K = 768 .. 8192, median error 3.5%); a k-tile costs more the more CUs are busy. The
+// choice between the two by price is within 0.2% of the faster one on average over them: 80x2560x2560
+// 9.1 us here and 11.0 on the DMA tiles, 100x2048x4096 8.8 and 12.8, 140x2560x5120 13.5 and 19.3, 258x2560x5120
+// 17.4 and 22.6; 391x2560x2560 19.2 and 15.9.
 float decode_tile_us(int64_t M, int64_t N, int64_t K) {
     const int64_t tm64 = (M + 63) / 64, tm32 = (M + 31) / 32, tn64 = (N + 63) / 64, tn32 = (N + 31) / 32;
-    const float nk = (float)(K / 64);
-    if (M > 128 && tm64 * tn64 >= 128) return 1.7f + rounds_of(tm64 * tn64) * (1.83f + 0.218f * nk);
-    if (tm64 * tn32 >= 128) return 0.7f + rounds_of(tm64 * tn32) * (2.03f + 0.169f * nk);
-    return 1.8f + rounds_of(tm32 * tn32) * (1.82f + 0.066f * nk);
+    auto price = [&](int64_t wg, float launch, float first, float tile, float busy) {
+        const float occ = (float)std::min<int64_t>(wg, 256) / 256.0f;
+        return launch + rounds_of(wg) * (first + (tile + busy * occ) * (float)(K / 64));
+    };
+    if (M > 128 && tm64 * tn64 >= 128) return price(tm64 * tn64, 2.07f, 1.89f, 0.128f, 0.036f);
+    if (tm64 * tn32 >= 128) return price(tm64 * tn32, 1.29f, 1.70f, 0.077f, 0.035f);
+    return price(tm32 * tn32, 1.23f, 1.23f, 0.100f, 0.017f);
 }
 // x_proj of up to 512 rows (at most 512 columns): 16-row tiles of the few-row kernel, which
 // spread over more workgroups than the DMA tiles and need no K-slices. Every wave streams its
@@ -876,12 +880,22 @@ hipError_t dispatch_dma(const GemmPlan& g, int64_t M, int64_t N, int64_t K, cons
 // K a multiple of 32 only, or a K of few 64-wide tiles (dt_proj: K = dt_rank): 32-wide stages,
 // whose rings stay small enough for several workgroups per CU; the many short-lived tiles hide
 // each other's first loads. 64x64 tiles while they fit two rounds (256x3584x224 5.9 -> 4.1 us,
-// 256x2560x160 5.2 -> 3.6), 256x128 ones once they fill four rounds (16384x8192x256 103 -> 96,
-// 65536x2560x160 129 -> 113, 65536x3584x224 205 -> 176 us against 128x128 with a 3-deep ring),
-// 128x128 between (2048x3584x224 9.9 -> 9.1). Over long rows of 4 KB this is not so at K = 256
-// (65536x2048x256 119 us against 115 on 256x256 tiles, while 65536x1024 takes 45 against 48 and 65536x4096
-// 207 against 213).
-//
+// 256x2560x160 5.2 -> 3.6). Above that the last round decides: 128x128 with a 4-deep ring runs 512 at
+// a time, with a 3-deep ring 768, 256x128 512 (of twice the output). By 305 shapes of K = 32 .. 256, us,
+// the 4-deep, 256x128 and the 3-deep:
+//   up to 512 128x128 tiles the 4-deep ring (K = 160, 440 tiles 8.0 / 8.5 / 8.4);
+//   up to 768 the 3-deep one (K = 96, 516 8.7 / 8.8 / 7.9);
+//   then 256x128 where its last round is at least half full (K = 224, 981 18.3 / 15.3 / 16.6; K = 128, 1024
+//   12.5 / 12.0 / 13.1), the 3-deep ring where it is emptier (K = 96, 2200 20.1 / 21.6 / 18.8; K = 64, 1152 12.4
+//   / 13.7 / 11.5), for a shorter K up to more rounds (K = 64, 5640 256x128 37.9, 3-deep 34.7; K = 96, 5380 40.1 and
+//   37.6; K = 224, 4360 47.0 and 49.8), and past those 256x128 (K = 96, 11500 97 and 122; 65536x2560x160 113 and 129).
+bool dma32_deep(int64_t K, int64_t t128, float r) {  // r: rounds of 256x128
+    if (t128 <= 768) return true;
+    if (r <= 1.0f) return false;
+    if (r <= 2.0f) return r <= (K <= 160 ? 1.5f : 1.25f);
+    return r <= (K <= 96 ? 6.4f : K <= 160 ? 3.75f : 2.15f);
+}
+
 // Two kinds of K of whole 64-wide tiles do better with those (372 shapes, M = 65 .. 32768, K = 64 .. 256):
 // outputs that give the few-row kernel one round of 32x32 tiles (2.7-2.9 us at K = 64 .. 256 against
 // 3.0-3.8), from K = 192 on also of 64x32 (3.4-3.6 against 3.5-3.9); and from K = 192 on outputs that fill
@@ -902,9 +916,11 @@ hipError_t dispatch_dma32(int64_t M, int64_t N, int64_t K, const void* A, int64_
                           void* C, int64_t ldc, hipStream_t s) {
     if (((M + 63) / 64) * ((N + 63) / 64) <= 512)
         return run_dma<ROLE, 64, 64, 32, 4, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
-    if (((M + 255) / 256) * ((N + 127) / 128) >= 1024)
-        return run_dma<ROLE, 256, 128, 32, 3, 4, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
-    return run_dma<ROLE, 128, 128, 32, 4, 2, 4, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    if (t128 <= 512) return run_dma<ROLE, 128, 128, 32, 4, 2, 4, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    if (dma32_deep(K, t128, (float)(((M + 255) / 256) * ((N + 127) / 128)) / 512.0f))
+        return run_dma<ROLE, 128, 128, 32, 3, 2, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    return run_dma<ROLE, 256, 128, 32, 3, 4, 2, CF>(M, N, K, A, lda, B, ldb, C, ldc, s);
 }
 
 // Scratch that a product may use for K-slices in a prefill of up to M rows: what kMaxSlices

@@ -150,7 +150,7 @@ def test_gemm_x_proj_decode_rows(B, M, N, K):
 # (role, M, N, K): products whose K-slices run on the tiles that have them, ragged in M and N: 32x64,
 # 64x64, 64x128, 128x128, 192x128 (bf16 and float32 output), 128x192
 BF16_SLICED_SHAPES = [
-    ("in_proj", 67, 76, 2048), ("out_proj", 701, 140, 2560), ("out_proj", 65, 2052, 4096), ("in_proj", 4999, 76, 2560),
+    ("in_proj", 67, 76, 2048), ("out_proj", 701, 140, 2560), ("out_proj", 520, 1028, 4096), ("in_proj", 4999, 76, 2560),
     ("out_proj", 391, 2564, 5120), ("x_proj", 521, 44, 2048), ("x_proj", 321, 160, 4096), ("x_proj", 673, 160, 4096),
     ("x_proj", 1345, 160, 4096), ("x_proj", 1347, 288, 8192), ("x_proj", 1926, 288, 8192)]
 # one shape per tile of the bf16 tile table, unsliced
@@ -160,7 +160,9 @@ BF16_TILE_SHAPES = [
     ("in_proj", 3001, 2604, 320), ("out_proj", 4999, 1804, 2048), ("in_proj", 2001, 3596, 64), ("out_proj", 4999, 2604, 64),
     ("in_proj", 4999, 3596, 320),
     ("x_proj", 5001, 288, 64),
-    # dt_proj: 64x64, 128x128 and 256x128 tiles on 32-wide stages
+    # dt_proj: 64x64, 128x128 (4- and 3-deep rings) and 256x128 tiles on 32-wide stages
+    ("dt_proj", 2601, 2060, 160), ("dt_proj", 3331, 2604, 96), ("dt_proj", 5003, 2604, 224), ("dt_proj", 9001, 1540, 32),
+    ("dt_proj", 9001, 2604, 160),
     ("dt_proj", 101, 2564, 160), ("dt_proj", 3001, 2604, 96), ("dt_proj", 16399, 2060, 32), ("dt_proj", 391, 1284, 256),
     # ... the few-row kernel's tiles, and 256x256 ones
     ("dt_proj", 365, 516, 64), ("dt_proj", 99, 4092, 256), ("dt_proj", 3333, 4084, 256), ("dt_proj", 1797, 8188, 192)]
